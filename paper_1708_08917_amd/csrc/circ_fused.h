@@ -426,11 +426,13 @@ void fc_fused_kernel(const float4* __restrict__ Wf, const float* __restrict__ x,
       float* creg = op + (rd * CPR + (PT >= CPR ? fc : min(fc, PT - 1))) * OPROW;   // region of this lane's column
       float2* xch = reinterpret_cast<float2*>(creg);
       if (rd == 0) more_weights(0);
-      // last chunk of a ragged q: a wave whose columns all lie past the last input block has nothing
-      // to transform (their operand rows meet zero weights and keep whatever finite values they hold)
+      // last chunk of a ragged q: a wave whose columns all belong to batches of matrix instructions
+      // that are skipped below has nothing to transform.  The other columns past the last input block
+      // are transformed (from the last block's values): their operand rows meet zero weights, but an
+      // unwritten row of LDS may hold a NaN, and 0 * NaN would reach every output.
       if constexpr (ragged) {
         const int jw0 = (rd * CPR + (wave * 64) / LC) / NP;       // first input block of this wave's columns
-        if (c * JC + jw0 >= q) continue;
+        if (c * JC + jw0 / JB * JB >= q) continue;
       }
       {
         float re[R1], im[R1];

@@ -88,6 +88,20 @@ def test_fc_one_or_two_vectors_split(p, q, k, batch):
     check(dw, O.fc_backward_dw(xt, dy, k), f"split gemv dw {q}x{p} k={k} B={batch}")
 
 
+# ---- two chunks of input blocks, the second one ragged: its columns past the last input block must not
+# reach the outputs, whatever an earlier kernel left in LDS (here: NaN from a layer on NaN inputs) ----------
+@pytest.mark.parametrize("p,q,k,batch", [(34, 10, 256, 14), (64, 6, 256, 341), (5, 33, 128, 6), (40, 17, 128, 207), (60, 34, 64, 133),
+                                         (9, 65, 64, 5)])
+def test_fc_forward_ragged_second_chunk_after_nan(p, q, k, batch):
+    w, x, b = rand_fc(p, q, k, batch)
+    wh, xd, bd = B.circ_precompute_spectra(G.dev(w)), G.dev(x), G.dev(b)
+    for kn, qn in ((256, 32), (64, 128)):
+        wn = B.circ_precompute_spectra(torch.full((64, qn, kn), float("nan"), device=G.DEV))
+        B.circ_fc_forward(wn, torch.full((64, qn * kn), float("nan"), device=G.DEV), None, None, 64, qn, kn)
+    y = B.circ_fc_forward(wh, xd, bd, None, p, q, k, B.EPI_BIAS)
+    check(y.cpu().numpy(), O.fc_forward(w, x, b), f"ragged second chunk {p}x{q} k={k} B={batch}")
+
+
 def test_fc_forward_bias_only_and_relu_only():
     w, x, b = rand_fc(4, 4, 16, 9)
     check(G.gpu_fc_forward(w, x, None, relu=True), O.fc_forward(w, x, None, relu=True), "relu only")

@@ -13,6 +13,7 @@
 #include "circ_gemm_split.h"
 #include "circ_fused.h"
 #include "circ_gemv.h"
+#include "circ_lane.h"
 #include "circ_conv_fused.h"
 #include "circ_conv_bwd.h"
 #include "circ_update.h"
@@ -519,6 +520,103 @@ inline bool use_fused_forward(int p, int q, int k, int batch) {
   return n_it <= 8 && l2_bytes <= kFusedMaxL2MiB * 1048576.0;
 }
 
+// Short blocks: the kernel of circ_lane.h.  mi tiles of 16 block rows per workgroup, ns slices of the
+// reduction (more than one: a second launch adds them), us: estimated time.
+struct LanePlan { int mi, ns; double us; };
+// Workgroups of a plan share 256 CUs.  c0: time of a call with almost no reduction; u1, u2: time of a step
+// of one wave per SIMD with one and with two tiles of 16 block rows (measured; 32 has one form only).
+inline LanePlan plan_lane(int p, int q, int k, int batch, size_t part_bytes) {
+  const double c0 = k == 4 ? 3.5 : k == 8 ? 4.0 : k == 16 ? 6.0 : 7.5;
+  const double u1 = k == 4 ? 0.16 : k == 8 ? 0.30 : k == 16 ? 0.70 : 2.1, u2 = k == 4 ? 0.30 : k == 8 ? 0.63 : 1.47;
+  const int w1 = k == 32 ? 4 : 8, per_cu = k <= 8 ? 2 : 1;      // waves and resident workgroups of the one-tile form
+  const double bt = double(cdiv(batch, 16)), t1 = double(cdiv(p, 16)) * bt, t2 = double(cdiv(p, 32)) * bt;
+  LanePlan best{1, 1, 0};
+  auto est1 = [&](int ns) {
+    const double wg = t1 * ns, nt = double(cdiv(cdiv(q, 4 * w1), ns));
+    return 2 + (c0 - 2) * double(cdiv((long long)wg, 256 * per_cu)) + (wg > 256 ? double(cdiv((long long)wg, 256)) : 1.0) * nt * (w1 / 4) * u1 +
+           (ns > 1 ? 3 + wg * k * 4e-4 + ns * k * 0.008 : 0.0);    // second launch, partial sums written and read
+  };
+  best.us = est1(1);
+  for (int ns = 2; ns <= 32 && t1 * ns <= 512 && q >= 4 * w1 * ns; ns *= 2)
+    if (size_t(t1) * ns * k * 256 * sizeof(float) <= part_bytes)
+      if (const double e = est1(ns); e < best.us) best = LanePlan{1, ns, e};
+  if (k <= 16 && t2 >= 512)
+    if (const double e = c0 + double(cdiv((long long)t2, 256)) * double(cdiv(q, 16)) * u2; e < best.us) best = LanePlan{2, 1, e};
+  return best;
+}
+// The rule between the routes for these block sizes is a comparison of estimated times, because no single
+// size decides: short rows and many tiles favour the one launch, long rows with large batches the
+// three kernels, whose contraction reuses operands over larger tiles.  Measured, other route -> this one:
+// 4096 -> 1000 k = 8 batch 256 27.7 -> 12.7 us, 512 x 2048 blocks of 8, batch 32: 66.5 -> 19.1 us, 4096 -> 4096
+// k = 16 batch 256 31.5 -> 20.2 us, 2112 -> 1280 k = 32 batch 700 30.0 -> 19.3 us (16-bit 33.0 -> 20.2 us); kept on the
+// other route: 4096 -> 4096 k = 32 batch 64 8.7 us against 24.5 us, k = 16 batch 1024 with 16-bit storage 35.6
+// against 53.4 us.  Over 200 shapes of 3 to 1024 batch rows the choice costs at most 9 % against the better one.
+// Times of the other routes, fitted to measurements (us):
+// fused kernel (32): every workgroup of two batch rows costs about the same per chunk of 64 input blocks;
+// three kernels: launches, the serial reduction of the contraction, its arithmetic, the passes over x and y.
+inline double other_route_us(int p, int q, int k, int batch, bool half) {
+  if (use_fused_forward(p, q, k, batch)) {
+    const double wg = double(cdiv(p, 16)) * double(cdiv(batch, 2)), t = 3 + double(cdiv(q, 64)) * (wg > 176 ? wg * 5.8 / 512 : 2.0);
+    return t > 5.5 ? t : 5.5;
+  }
+  const double mb = double(p + q) * k * batch * (half ? 2e-6 : 4e-6);
+  if (half) return 11 + 0.024 * q + 0.8 * mb;
+  const double serial = 0.031 * q, arith = 8.5e-9 * 8 * double(p) * q * (k / 2 + 1) * batch;
+  return 7 + (serial > arith ? serial : arith) + 0.6 * mb;
+}
+// part_bytes: workspace that the partial sums may take (what the call asks for on any route)
+inline bool use_lane_forward(int p, int q, int k, int batch, bool half, size_t part_bytes, LanePlan* plan = nullptr) {
+  if (!(k == 4 || k == 8 || k == 16 || k == 32) || batch <= 2) return false;
+  // byte offsets into 16 rows of x and into the spectrum section are kept in 31 bits
+  if ((long long)q * k > (1ll << 24) || (long long)p * q * (k / 2 + 1) > (1ll << 27)) return false;
+  const LanePlan pl = plan_lane(p, q, k, batch, part_bytes);
+  if (plan) *plan = pl;
+  return pl.us <= other_route_us(p, q, k, batch, half);
+}
+// HM: 0 fp32 (spec = spectrum section [f][j][i]), 1 fp16, 2 bfloat16 (spec = conjugated section [f][j][i])
+template <int K, int MI, int HM>
+hipError_t launch_lane_m(const LanePlan& pl, const void* spec, const void* x, const float* bias, void* y, int p, int q, int batch,
+                         int relu, void* workspace, hipStream_t s) {
+  using Sh = LaneShape<K, MI>;
+  static LdsOptIn opted_in;
+  if (ensure_lds(&fc_lane_kernel<K, MI, HM>, Sh::lds_bytes(), opted_in) != hipSuccess) return hipErrorInvalidValue;
+  const FusedTileMap tm = make_fused_tile_map(p, q, K, 16 * MI, 8, batch);
+  const int nt = (int)cdiv(cdiv(q, 4 * Sh::W), pl.ns);
+  float* part = pl.ns > 1 ? static_cast<float*>(workspace) : nullptr;
+  hipLaunchKernelGGL((fc_lane_kernel<K, MI, HM>), dim3(tm.grid, (unsigned)pl.ns), dim3(Sh::NT), Sh::lds_bytes(), s, spec, x, bias, y,
+                     p, q, batch, tm, relu, part, nt);
+  if (part) {
+    if (hipGetLastError() != hipSuccess) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((lane_finish_kernel<K, HM>), dim3((unsigned)(tm.n_it * tm.n_bt)), dim3(256), 0, s, part, bias, y, p, batch,
+                       tm.n_it, pl.ns, relu);
+  }
+  return hipGetLastError();
+}
+template <int K, int HM>
+hipError_t launch_lane_k(const LanePlan& pl, const void* spec, const void* x, const float* bias, void* y, int p, int q, int batch,
+                         int relu, void* workspace, hipStream_t s) {
+  if constexpr (K <= 16) {
+    if (pl.mi == 2) return launch_lane_m<K, 2, HM>(pl, spec, x, bias, y, p, q, batch, relu, workspace, s);
+  }
+  return launch_lane_m<K, 1, HM>(pl, spec, x, bias, y, p, q, batch, relu, workspace, s);
+}
+template <int HM>
+hipError_t launch_lane_h(const LanePlan& pl, int k, const void* spec, const void* x, const float* bias, void* y, int p, int q,
+                         int batch, int relu, void* workspace, hipStream_t s) {
+  switch (k) {
+    case 4: if constexpr (HM == 0) return launch_lane_k<4, HM>(pl, spec, x, bias, y, p, q, batch, relu, workspace, s); else return hipErrorInvalidValue;
+    case 8: return launch_lane_k<8, HM>(pl, spec, x, bias, y, p, q, batch, relu, workspace, s);
+    case 16: return launch_lane_k<16, HM>(pl, spec, x, bias, y, p, q, batch, relu, workspace, s);
+    case 32: return launch_lane_k<32, HM>(pl, spec, x, bias, y, p, q, batch, relu, workspace, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+hipError_t launch_lane_half(const LanePlan& pl, bool bf, int k, const void* spec, const void* x, const float* bias, void* y, int p,
+                            int q, int batch, int relu, void* workspace, hipStream_t s) {
+  return bf ? launch_lane_h<2>(pl, k, spec, x, bias, y, p, q, batch, relu, workspace, s)
+            : launch_lane_h<1>(pl, k, spec, x, bias, y, p, q, batch, relu, workspace, s);
+}
+
 // Batch <= 2 on few block rows with long rows: split the input blocks over several workgroups per
 // block row (two launches, partial spectra through the workspace).  Returns the number of splits
 // (1 = single launch).  Each split keeps at least 8 input blocks; the split pays for its second
@@ -721,6 +819,10 @@ circ_status circ_fc_forward(const void* w_hat, const float* x, const float* bias
       return CIRC_EHIP;
     return CIRC_OK;
   }
+  LanePlan lane;
+  if (use_lane_forward(p, q, k, batch, false, need, &lane))
+    return launch_lane_h<0>(lane, k, blob_at<float2>(w_hat, bl.fwd), x, use_bias ? bias : nullptr, y, p, q, batch,
+                            (epilogue & CIRC_EPI_RELU) ? 1 : 0, workspace, s) == hipSuccess ? CIRC_OK : CIRC_EHIP;
   if (use_fused_forward(p, q, k, batch)) {
     const float4* wfu = blob_at<float4>(w_hat, bl.fused_fwd);
     if (launch_fused(k, wfu, x, use_bias ? bias : nullptr, y, p, q, batch, (epilogue & CIRC_EPI_RELU) ? 1 : 0, s) !=
@@ -864,8 +966,11 @@ circ_status fc_backward_impl(const void* w_hat, const float* x, const float* dy,
   const bool want_dw = dw || w_upd;
   const bool dw_shares_dy = want_dw && cgemm_takes_tiled(k, p, q, batch, ksplit);
   bool have_dyh = false;   // bufy holds dY^[f][i][b]
+  LanePlan lane;
   if (dx && batch <= 2 && gemv_k(k)) {
     if (launch_gemv(k, blob_at<float2>(w_hat, bl.gemv_bwd), dy, nullptr, dx, q, p, batch, 0, workspace, s) != hipSuccess) return CIRC_EHIP;
+  } else if (dx && use_lane_forward(q, p, k, batch, false, xa + ya, &lane)) {
+    if (launch_lane_h<0>(lane, k, wb, dy, nullptr, dx, q, p, batch, 0, workspace, s) != hipSuccess) return CIRC_EHIP;
   } else if (dx && use_fused_forward(q, p, k, batch)) {
     if (launch_fused(k, blob_at<float4>(w_hat, bl.fused_bwd), dy, nullptr, dx, q, p, batch, 0, s) != hipSuccess)
       return CIRC_EHIP;
@@ -1577,6 +1682,12 @@ circ_status fc_forward_half(bool bf, const void* w_hat, const void* x, const flo
                ? CIRC_OK
                : CIRC_EHIP;
   }
+  LanePlan lane;
+  if (use_lane_forward(p, q, k, batch, true, fc_workspace_bytes_half(p, q, k, batch), &lane))
+    return launch_lane_half(lane, bf, k, static_cast<const char*>(w_hat) + half_blob(p, q, k).bwd, x, use_bias ? bias : nullptr, y, p, q,
+                            batch, (epilogue & CIRC_EPI_RELU) ? 1 : 0, workspace, s) == hipSuccess
+               ? CIRC_OK
+               : CIRC_EHIP;
   if (use_fused_forward(p, q, k, batch)) {
     // one launch: 16-bit loads of x and of the packed operands, fp32 inside, 16-bit store of y
     const void* wfu = static_cast<const char*>(w_hat) + half_blob(p, q, k).fused_fwd;
@@ -1656,7 +1767,9 @@ circ_status fc_backward_half(bool bf, const void* w_hat, const void* x, const vo
   // Backward-data alone takes dY^[f][b][i], which its contraction reads without the transposition.
   // (The one-launch kernels of small problems read dy itself; the batch <= 2 one may use the start
   // of the workspace for its partial spectra, so the transform for the weight gradient follows it.)
-  const bool dx_one_launch = batch <= 2 || use_fused_forward(q, p, k, batch);
+  LanePlan lane;
+  const bool dx_lane = dx && use_lane_forward(q, p, k, batch, true, 2 * (xs + ys), &lane);
+  const bool dx_one_launch = batch <= 2 || dx_lane || use_fused_forward(q, p, k, batch);
   RowMap myt{batch, p, (long long)p * k, (long long)k, 0, 1};
   if (dw && dx && !dx_one_launch) {
     if (launch_rfft_half(k, hm, bf, dy, dyt, myt, yrows, yrows, 1.0f, s) != hipSuccess) return CIRC_EHIP;
@@ -1668,6 +1781,9 @@ circ_status fc_backward_half(bool bf, const void* w_hat, const void* x, const vo
     const __half2* wt = reinterpret_cast<const __half2*>(static_cast<const char*>(w_hat) + hb.bwd);
     if (batch <= 2) {
       if (launch_gemv_half(bf, k, static_cast<const char*>(w_hat) + hb.gemv_bwd, dy, nullptr, dx, q, p, batch, 0, workspace, s) != hipSuccess)
+        return CIRC_EHIP;
+    } else if (dx_lane) {
+      if (launch_lane_half(lane, bf, k, static_cast<const char*>(w_hat) + hb.fwd, dy, nullptr, dx, q, p, batch, 0, workspace, s) != hipSuccess)
         return CIRC_EHIP;
     } else if (use_fused_forward(q, p, k, batch)) {
       // small problems: the fused kernel on the transposed grid's operands, one launch

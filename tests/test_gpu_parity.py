@@ -468,6 +468,31 @@ def test_fc_forward_half_shapes(p, q, k, batch, dtype):
     check_half(gpu_fc_forward_half(w, xt, None, False), O.fc_forward(w, xr), "plain " + what, dtype)
 
 
+# ---- short blocks, the one-launch kernel of 16x16 tiles: edges of its tiles (16 block rows, 16 batch rows),
+# of its steps (4 input blocks, 4 waves x 8 of them), slices of the reduction in a second launch (few tiles,
+# long rows) and the form with two tiles of block rows per workgroup (at least 512 of those).  Sums of
+# at most 2000 fp32 terms: the gates of the other tests hold unchanged.
+@pytest.mark.parametrize("p,q,k,batch", [
+    (1, 1, 4, 3), (15, 3, 4, 16), (17, 130, 4, 17), (65, 33, 4, 2731), (4, 700, 4, 18),
+    (16, 4, 8, 15), (33, 31, 8, 33), (1, 33, 8, 3), (66, 33, 8, 2731), (5, 520, 8, 19),
+    (31, 5, 16, 16), (48, 65, 16, 31), (65, 34, 16, 2731), (7, 260, 16, 20),
+    (129, 1, 32, 17), (144, 15, 32, 35), (131, 18, 32, 49), (40, 66, 32, 700),
+])
+def test_fc_short_blocks(p, q, k, batch):
+    w, x, b = rand_fc(p, q, k, batch)
+    what = f"short blocks {p}x{q} k={k} B={batch}"
+    check(G.gpu_fc_forward(w, x, b, relu=True), O.fc_forward(w, x, b, relu=True), "fwd " + what)
+    wt, _, _ = rand_fc(q, p, k, 1, bias=False)
+    dx, _ = G.gpu_fc_backward(wt, None, x, need_dw=False)          # backward-data of the q x p layer: p outputs, q inputs
+    check(dx, O.fc_backward_dx(wt, x), "dx " + what)
+    if k >= 8:
+        for dtype in HALF_DTYPES:
+            xt, xr = to_half(x, dtype)
+            check_half(gpu_fc_forward_half(w, xt, b, True), O.fc_forward(w, xr, b, True), "fwd " + what, dtype)
+            dxh, _ = B.circ_fc_backward_f16(B.circ_precompute_spectra_f16(G.dev(wt), dtype=dtype), None, xt, q, p, k, need_dw=False)
+            check_half(dxh.float().cpu().numpy(), O.fc_backward_dx(wt, xr), "dx " + what, dtype)
+
+
 def test_fc_forward_bf16_large_inputs():
     """Inputs far outside the fp16 range (|x| k up to 4e7) are fine in bfloat16."""
     p, q, k, batch = 3, 4, 64, 9

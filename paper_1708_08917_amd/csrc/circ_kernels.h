@@ -744,7 +744,7 @@ __global__ __launch_bounds__(64) void cgemm_kernel(const float2* __restrict__ A,
 }
 
 // -------------------------------------------------------------------------------------
-// CONV contraction, one thread per (frequency, image, output pixel), IT output channel
+// CONV contraction, one lane per (frequency, image, output pixel), IT = 4 or 8 output channel
 // blocks at a time:
 //   Yh[f][i][n][ho][wo] = sum_{dh,dw,j} What[dh*r+dw][f][j][i] * Xh[f][j][n][ho*stride+dh-pad][wo*stride+dw-pad]
 // with zero spectra outside the image (the channel FFT of a zero pixel is zero, so the
@@ -754,46 +754,219 @@ __global__ __launch_bounds__(64) void cgemm_kernel(const float2* __restrict__ A,
 // stride: the filter moves `stride` input pixels per output pixel (tap = ho*stride + dh - pad).
 // dil: the input grid is the H x W one with dil-1 zeros inserted between its pixels (a tap u
 // reads input pixel u/dil when dil divides u, zero otherwise) - backward-data of a strided layer.
-template <int IT>
-__global__ void conv_contract_kernel(const float2* __restrict__ What, const float2* __restrict__ Xh,
-                                     float2* __restrict__ Yh, int p, int q, int NF, int Nimg, int H,
-                                     int W, int Ho, int Wo, int r, int pad, int flip, int stride, int dil) {
+//
+// v_mfma_f32_4x4x1_16B_f32 multiplies, in each of 16 groups of 4 lanes, 4 output blocks by 4 pixels: lane l
+// supplies the weight of block i0 + l % 4 and the spectrum value of its own pixel, and receives the sums
+// of its own pixel - the layout of one thread per pixel, at twice the rate of the vector ALUs (64 x 4
+// products in 8 cycles against 16) and with a 1-cache-line load in place of scalar loads of the weights.
+// Serves 1x1 filters, backward-data of strided layers (dil > 1) and images too wide for the staged kernel
+// below.  What is left is memory latency, so the (tap, group of JQ input blocks) pairs form one
+// sequence, and the values of the next pair are requested before the current one is multiplied.  Taps
+// outside the image read a valid address and are replaced by zeros.  Lanes past the last pixel take
+// part with the last one (a group needs all of its weights).
+// 384 -> 384 channels of blocks of 96, 3x3, 13x13, batch 32 (5408 pixels x 49 bins): 21.3 us on the vector
+// ALUs with every load waiting for the one before it, 17.7 us in this form (12.5 us staged in LDS, below).
+template <int IT, int JQ, bool DIL>
+__global__ __launch_bounds__(256) void conv_contract_kernel(const float2* __restrict__ What, const float2* __restrict__ Xh,
+                                                            float2* __restrict__ Yh, int p, int q, int NF, int Nimg, int H,
+                                                            int W, int Ho, int Wo, int r, int pad, int flip, int stride, int dil) {
   const long long npix = (long long)Nimg * Ho * Wo;
-  const long long opix = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (opix >= npix) return;
+  const long long lpix = (long long)blockIdx.x * blockDim.x + threadIdx.x, opix = lpix < npix ? lpix : npix - 1;
   const int f = blockIdx.y, i0 = blockIdx.z * IT;
-  const int n = int(opix / (Ho * Wo)), rem = int(opix % (Ho * Wo));
-  const int ho = rem / Wo, wo = rem % Wo;
-  float2 acc[IT];
+  int n, rem;
+  if (npix <= 0x7fffffff) {                                     // (uniform; the 64-bit division is a long one)
+    n = int(unsigned(opix) / unsigned(Ho * Wo));
+    rem = int(unsigned(opix) - unsigned(n) * unsigned(Ho * Wo));
+  } else {
+    n = int(opix / (Ho * Wo));
+    rem = int(opix % (Ho * Wo));
+  }
+  const int ho = int(unsigned(rem) / unsigned(Wo)), wo = rem - ho * Wo;
+  const int h0 = ho * stride - pad, w0 = wo * stride - pad;
+  const unsigned plane = unsigned(Nimg) * unsigned(H * W), img = unsigned(n) * unsigned(H * W);
+  const float2* Xf = Xh + (long long)f * q * plane;
+  constexpr int IG = IT / 4;
+  unsigned wi[IG];                                              // this lane's output blocks
 #pragma unroll
-  for (int ii = 0; ii < IT; ++ii) acc[ii] = make_float2(0.f, 0.f);
-  for (int dh = 0; dh < r; ++dh) {
-    for (int dw = 0; dw < r; ++dw) {
-      int hi = ho * stride + dh - pad, wi = wo * stride + dw - pad;
-      bool inb = hi >= 0 && wi >= 0;
-      if (dil > 1) {
-        inb = inb && hi % dil == 0 && wi % dil == 0;
-        hi /= dil;
-        wi /= dil;
+  for (int g = 0; g < IG; ++g) wi[g] = unsigned(min(i0 + 4 * g + int(threadIdx.x & 3), p - 1));
+  floatx4 accR[IG], accI[IG];
+#pragma unroll
+  for (int g = 0; g < IG; ++g) {
+    accR[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+    accI[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+
+  float2 next[JQ], wnext[JQ][IG];
+  bool next_in;
+  const int taps = r * r;
+  auto request = [&](int t, int dh, int dw, int j0) {
+    int hi = h0 + dh, wj = w0 + dw;
+    bool in = true;
+    if constexpr (DIL) {
+      const int hq = hi / dil, wq = wj / dil;
+      in = hi >= 0 && wj >= 0 && hq * dil == hi && wq * dil == wj;
+      hi = hq;
+      wj = wq;
+    }
+    next_in = in && unsigned(hi) < unsigned(H) && unsigned(wj) < unsigned(W);
+    const unsigned o = img + (next_in ? unsigned(hi * W + wj) : 0u);
+    const float2* wg = What + ((long long)(flip ? taps - 1 - t : t) * NF + f) * q * p;
+#pragma unroll
+    for (int jj = 0; jj < JQ; ++jj) {
+      const int j = min(j0 + jj, q - 1);
+      next[jj] = (Xf + (long long)j * plane)[o];
+#pragma unroll
+      for (int g = 0; g < IG; ++g) wnext[jj][g] = (wg + j * p)[wi[g]];
+    }
+  };
+  int t = 0, dh = 0, dw = 0, j0 = 0;
+  request(0, 0, 0, 0);
+  while (t < taps) {
+    float2 x[JQ], w[JQ][IG];
+#pragma unroll
+    for (int jj = 0; jj < JQ; ++jj) {
+      x[jj] = next_in ? next[jj] : make_float2(0.f, 0.f);
+#pragma unroll
+      for (int g = 0; g < IG; ++g) w[jj][g] = wnext[jj][g];
+    }
+    const int jc = j0;
+    // the next pair (behind the last one: the first tap again)
+    j0 += JQ;
+    if (j0 >= q) {
+      j0 = 0;
+      ++t;
+      if (++dw == r) {
+        dw = 0;
+        if (++dh == r) dh = 0;
       }
-      inb = inb && hi < H && wi < W;
-      const int g = flip ? r * r - 1 - (dh * r + dw) : dh * r + dw;
-      const float2* wg = What + ((long long)g * NF + f) * q * p;
-      for (int j = 0; j < q; ++j) {
-        float2 xv = make_float2(0.f, 0.f);
-        if (inb) xv = Xh[(((long long)f * q + j) * Nimg + n) * H * W + hi * W + wi];
+    }
+    request(t < taps ? t : 0, dh, dw, j0);
 #pragma unroll
-        for (int ii = 0; ii < IT; ++ii) {
-          float2 wv = wg[j * p + min(i0 + ii, p - 1)];
-          acc[ii].x += wv.x * xv.x - wv.y * xv.y;
-          acc[ii].y += wv.x * xv.y + wv.y * xv.x;
+    for (int jj = 0; jj < JQ; ++jj) {
+      if (jc + jj < q) {
+#pragma unroll
+        for (int g = 0; g < IG; ++g) {
+          accR[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[jj][g].x, x[jj].x, accR[g], 0, 0, 0);
+          accI[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[jj][g].x, x[jj].y, accI[g], 0, 0, 0);
+        }
+#pragma unroll
+        for (int g = 0; g < IG; ++g) {
+          accR[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[jj][g].y, -x[jj].y, accR[g], 0, 0, 0);
+          accI[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[jj][g].y, x[jj].x, accI[g], 0, 0, 0);
         }
       }
     }
   }
+  if (lpix >= npix) return;
 #pragma unroll
   for (int ii = 0; ii < IT; ++ii)
-    if (i0 + ii < p) Yh[(((long long)f * p + i0 + ii) * Nimg + n) * Ho * Wo + rem] = acc[ii];
+    if (i0 + ii < p) Yh[(((long long)f * p + i0 + ii) * Nimg + n) * Ho * Wo + rem] = make_float2(accR[ii / 4][ii % 4], accI[ii / 4][ii % 4]);
+}
+
+// The same contraction with the spectra staged in LDS (undilated input).  A workgroup takes, for one
+// frequency and one group of IT output blocks, the output rows [ho0, ho0 + BR) of G images: it stages
+// the input rows under them of all q blocks, zero columns and rows around the image included, and the
+// frequency's weights in one burst of loads, and everything after the barrier runs from LDS: per (tap,
+// input block) and 64 pixels two LDS reads and four 4x4x1 matrix instructions per 4 output blocks.  The kernel
+// above waits for memory at every tap, and its nine reads of a value pass through the cache one by one.
+// LDS: q planes of `pstride` values, then r*r*q*IT weights.  mul_*: ceil(2^32 / d) for the divisions by
+// rows_in*(W+2*pad), W+2*pad, BR*Wo and Wo (indices and divisors below 2^16: exact).
+template <int IT>
+__global__ __launch_bounds__(256) void conv_contract_lds_kernel(const float2* __restrict__ What, const float2* __restrict__ Xh,
+                                                                float2* __restrict__ Yh, int p, int q, int NF, int Nimg, int H,
+                                                                int W, int Ho, int Wo, int r, int pad, int flip, int stride, int G,
+                                                                int BR, int nbands, int pstride, unsigned mul_pl, unsigned mul_wp,
+                                                                unsigned mul_px, unsigned mul_wo) {
+  extern __shared__ __attribute__((aligned(16))) float2 cxs[];
+  constexpr int IG = IT / 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), f = blockIdx.y;
+  const int i0 = blockIdx.z * IT, chunk = blockIdx.x, n0 = chunk / nbands * G, ho0 = (chunk % nbands) * BR;
+  const int Wp = W + 2 * pad, rows_in = (BR - 1) * stride + r, pl = rows_in * Wp, taps = r * r;
+  const unsigned HW = unsigned(H) * unsigned(W);
+  float2* ws = cxs + q * pstride;
+
+  // weights [tap][j][i], the reflected filter's tap order with flip; blocks past p repeat the last one
+  for (int e = tid; e < taps * q * IT; e += 256) {
+    const int i = e % IT, tj = e / IT, t = tj / q, j = tj - t * q;
+    ws[e] = What[((long long)(flip ? taps - 1 - t : t) * NF + f) * q * p + (long long)j * p + min(i0 + i, p - 1)];
+  }
+  const int hfirst = ho0 * stride - pad;
+  for (int e = tid; e < G * pl; e += 256) {
+    const int g = int(__umulhi(unsigned(e), mul_pl)), rem = e - g * pl, row = int(__umulhi(unsigned(rem), mul_wp));
+    const int hi = hfirst + row, wi = rem - row * Wp - pad, n = n0 + g;
+    const bool in = unsigned(hi) < unsigned(H) && unsigned(wi) < unsigned(W) && n < Nimg;
+    const unsigned o = in ? unsigned(n) * HW + unsigned(hi * W + wi) : 0u;
+    const float2* src = Xh + (long long)f * q * Nimg * HW;
+    int j = 0;
+    for (; j + 4 <= q; j += 4) {
+      float2 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = (src + (long long)(j + u) * Nimg * HW)[o];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) cxs[(j + u) * pstride + e] = in ? v[u] : make_float2(0.f, 0.f);
+    }
+    for (; j < q; ++j) {
+      const float2 v = (src + (long long)j * Nimg * HW)[o];
+      cxs[j * pstride + e] = in ? v : make_float2(0.f, 0.f);
+    }
+  }
+  __syncthreads();
+
+  const int npx = BR * Wo, total = G * npx;
+  const float2* wl = ws + (lane & 3);
+  for (int g0 = wave * 64; g0 < total; g0 += 256) {
+    const int px = min(g0 + lane, total - 1);                   // lanes past the end take part with the last pixel
+    const int g = int(__umulhi(unsigned(px), mul_px)), rem = px - g * npx, hl = int(__umulhi(unsigned(rem), mul_wo)), wo = rem - hl * Wo;
+    const float2* xl = cxs + g * pl + (hl * Wp + wo) * stride;
+    floatx4 accR[IG], accI[IG];
+#pragma unroll
+    for (int h = 0; h < IG; ++h) {
+      accR[h] = floatx4{0.f, 0.f, 0.f, 0.f};
+      accI[h] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    const float2* wt = wl;
+    for (int dh = 0; dh < r; ++dh) {
+      for (int dw = 0; dw < r; ++dw) {
+        const float2* xt = xl + dh * Wp + dw;
+        auto block = [&](auto NJ) {                             // NJ input blocks: operands first, then the products
+          constexpr int N = decltype(NJ)::value;
+          float2 x[N], w[N][IG];
+#pragma unroll
+          for (int u = 0; u < N; ++u) {
+            x[u] = xt[u * pstride];
+#pragma unroll
+            for (int h = 0; h < IG; ++h) w[u][h] = wt[u * IT + 4 * h];
+          }
+#pragma unroll
+          for (int u = 0; u < N; ++u) {
+#pragma unroll
+            for (int h = 0; h < IG; ++h) {
+              accR[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[u][h].x, x[u].x, accR[h], 0, 0, 0);
+              accI[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[u][h].x, x[u].y, accI[h], 0, 0, 0);
+            }
+#pragma unroll
+            for (int h = 0; h < IG; ++h) {
+              accR[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[u][h].y, -x[u].y, accR[h], 0, 0, 0);
+              accI[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[u][h].y, x[u].x, accI[h], 0, 0, 0);
+            }
+          }
+          xt += N * pstride;
+          wt += N * IT;
+        };
+        int j = 0;
+        for (; j + 4 <= q; j += 4) block(std::integral_constant<int, 4>{});
+        for (; j + 2 <= q; j += 2) block(std::integral_constant<int, 2>{});
+        if (j < q) block(std::integral_constant<int, 1>{});
+      }
+    }
+    const int n = n0 + g, ho = ho0 + hl;
+    if (g0 + lane < total && n < Nimg && ho < Ho) {
+#pragma unroll
+      for (int ii = 0; ii < IT; ++ii)
+        if (i0 + ii < p)
+          Yh[(((long long)f * p + i0 + ii) * Nimg + n) * Ho * Wo + ho * Wo + wo] = make_float2(accR[ii / 4][ii % 4], accI[ii / 4][ii % 4]);
+    }
+  }
 }
 
 }  // namespace circ

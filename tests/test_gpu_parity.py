@@ -603,6 +603,25 @@ def test_cfg4_forward_half(dtype):
         check_half(y[n:n + 1], O.conv_forward(w, xr[n:n + 1], pad=c.pad), f"cfg4 image {n}", dtype)
 
 
+# ---- the three-kernel CONV route's contraction: groups of 4 and 8 output blocks with and without a remainder,
+# groups of 1, 2 and 4 input blocks, several images and several bands of rows per chunk (last ones short),
+# fewer pixels than lanes, strides; 1x1 filters and rows too wide for LDS take the unstaged kernel.
+@pytest.mark.parametrize("N,p,q,k,H,W,r,pad,stride", [
+    (1, 1, 1, 16, 3, 3, 3, 1, 1), (5, 4, 3, 16, 13, 13, 3, 1, 1), (7, 5, 7, 8, 9, 11, 3, 1, 1), (3, 9, 4, 16, 10, 7, 5, 2, 1),
+    (2, 8, 9, 4, 40, 37, 3, 0, 1), (33, 2, 2, 12, 5, 5, 3, 1, 1), (2, 3, 5, 16, 21, 18, 3, 1, 2), (1, 7, 1, 8, 130, 90, 3, 1, 1),
+    (3, 5, 4, 16, 9, 9, 1, 0, 1), (1, 2, 3, 4, 3, 2100, 3, 1, 1), (2, 6, 33, 4, 8, 8, 3, 1, 1), (4, 4, 4, 96, 13, 13, 3, 1, 1),
+])
+def test_conv_contraction(N, p, q, k, H, W, r, pad, stride):
+    w = (RNG.standard_normal((r, r, p, q, k)) / np.sqrt(r * r * q * k)).astype(np.float32)
+    x = RNG.uniform(-1, 1, (N, q * k, H, W)).astype(np.float32)
+    what = f"contraction N={N} {p}x{q} k={k} {H}x{W} r={r} pad={pad} stride={stride}"
+    check(G.gpu_conv_forward(w, x, None, pad=pad, stride=stride), O.conv_forward(w, x, None, pad=pad, stride=stride), "fwd " + what)
+    Ho, Wo = O.conv_out_size(H, r, pad, stride), O.conv_out_size(W, r, pad, stride)
+    dy = RNG.uniform(-1, 1, (N, p * k, Ho, Wo)).astype(np.float32)
+    dx, _ = G.gpu_conv_backward(w, x, dy, pad, need_dw=False, stride=stride)
+    check(dx, O.conv_backward_dx(w, dy, H, W, pad, stride), "dx " + what)
+
+
 # ---- stride > 1 and even filter sizes (Eq. 6 is the stride-1 case) ---------------------------
 @pytest.mark.parametrize("N,p,q,k,H,W,r,pad,stride", [
     (2, 2, 3, 8, 9, 8, 3, 1, 2), (3, 1, 2, 16, 7, 7, 3, 0, 2), (2, 4, 4, 64, 28, 28, 3, 1, 2), (2, 2, 2, 64, 13, 12, 3, 1, 3),

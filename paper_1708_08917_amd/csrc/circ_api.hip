@@ -8,6 +8,7 @@
 
 #include "../../include/circ.h"
 #include "circ_kernels.h"
+#include "circ_chan.h"
 #include "circ_dft.h"
 #include "circ_gemm.h"
 #include "circ_gemm_split.h"
@@ -171,20 +172,58 @@ bool launch_rfft_stream(const float* in, float2* out, const RowMap& map, long lo
   }
 }
 
+// Transforms down the channel axis (circ_chan.h): P columns of two pixels and R2 threads each per workgroup;
+// at least 512 workgroups where the image is large enough, and rows of at least 32 pixels (128 bytes) otherwise.
+template <int K>
+inline int plan_chan(long long nrows) {
+  constexpr int R2 = radix2_of(K);
+  int P = 64;
+  while (P > 8 && (P * R2 > 512 || size_t(K) * (P + 1) * sizeof(float2) > kFftMaxLdsBytes)) P >>= 1;
+  while (P > 16 && cdiv(nrows, 2 * P) < 512) P >>= 1;
+  return P;
+}
+template <int K, int HMODE>
+hipError_t launch_rfft_chan(const void* in, float2* out, const RowMap& map, long long nrows, long long out_fstride, hipStream_t s) {
+  const int P = plan_chan<K>(nrows);
+  const dim3 grid((unsigned)cdiv(nrows, 2 * P)), block(P * radix2_of(K));
+  const size_t lds = size_t(K) * (P + 1) * sizeof(float2);
+  if (map.n0 % 2 == 0)
+    hipLaunchKernelGGL((rfft_chan_kernel<K, HMODE, true>), grid, block, lds, s, in, out, map, nrows, out_fstride, P);
+  else
+    hipLaunchKernelGGL((rfft_chan_kernel<K, HMODE, false>), grid, block, lds, s, in, out, map, nrows, out_fstride, P);
+  return hipGetLastError();
+}
+template <int K, int HMODE>
+hipError_t launch_irfft_chan(const float2* in, void* out, const RowMap& map, long long nrows, long long in_fstride,
+                             const float* bias, long long bias_div, int relu, hipStream_t s) {
+  const int P = plan_chan<K>(nrows);
+  const dim3 grid((unsigned)cdiv(nrows, 2 * P)), block(P * radix2_of(K));
+  const size_t lds = size_t(K) * (P + 1) * sizeof(float2);
+  const bool spair = (nrows | in_fstride) % 2 == 0 && aligned16(in);
+  if (map.n0 % 2 == 0 && spair)
+    hipLaunchKernelGGL((irfft_chan_kernel<K, HMODE, true, true>), grid, block, lds, s, in, out, map, nrows, in_fstride, P, bias,
+                       bias_div, relu);
+  else if (spair)
+    hipLaunchKernelGGL((irfft_chan_kernel<K, HMODE, false, true>), grid, block, lds, s, in, out, map, nrows, in_fstride, P, bias,
+                       bias_div, relu);
+  else
+    hipLaunchKernelGGL((irfft_chan_kernel<K, HMODE, false, false>), grid, block, lds, s, in, out, map, nrows, in_fstride, P, bias,
+                       bias_div, relu);
+  return hipGetLastError();
+}
+
 template <int K>
 hipError_t launch_rfft_k(bool rows_fast, const float* in, float2* out, const RowMap& map, long long nrows,
                          long long out_fstride, int n_grids, long long in_gstride, long long out_gstride,
                          float scale, int conj, hipStream_t s) {
-  if (!rows_fast && n_grids == 1 && launch_rfft_stream<K, 0>(in, out, map, nrows, out_fstride, scale, conj, s))
+  // (rows that are adjacent in memory: images, one grid, neither scaled nor conjugated)
+  if (rows_fast) return launch_rfft_chan<K, 0>(in, out, map, nrows, out_fstride, s);
+  if (n_grids == 1 && launch_rfft_stream<K, 0>(in, out, map, nrows, out_fstride, scale, conj, s))
     return hipGetLastError();
   FftPlan pl = plan_fft(K, nrows);
   dim3 grid((unsigned)cdiv(nrows, 2 * pl.P), (unsigned)n_grids);
-  if (rows_fast)
-    hipLaunchKernelGGL((rfft_kernel<K, true>), grid, dim3(pl.NT), pl.lds, s, in, out, map, nrows, out_fstride,
-                       in_gstride, out_gstride, pl.P, scale, conj);
-  else
-    hipLaunchKernelGGL((rfft_kernel<K, false>), grid, dim3(pl.NT), pl.lds, s, in, out, map, nrows, out_fstride,
-                       in_gstride, out_gstride, pl.P, scale, conj);
+  hipLaunchKernelGGL((rfft_kernel<K>), grid, dim3(pl.NT), pl.lds, s, in, out, map, nrows, out_fstride, in_gstride, out_gstride,
+                     pl.P, scale, conj);
   return hipGetLastError();
 }
 
@@ -192,11 +231,12 @@ template <int K>
 hipError_t launch_irfft_k(bool rows_fast, const float2* in, float* out, const RowMap& map, long long nrows,
                           long long in_fstride, float scale, const float* bias, long long bias_div, int relu,
                           int nparts, long long part_stride, hipStream_t s) {
+  if (rows_fast) return launch_irfft_chan<K, 0>(in, out, map, nrows, in_fstride, bias, bias_div, relu, s);   // images: one part, scale 1
   if constexpr (stream_k<K>()) {
     // long runs of contiguous rows: the streaming form (65,536 rows of 256)
     constexpr int P = 4096 / K;
     const long long ntiles = cdiv(nrows, 2 * P);
-    if (!rows_fast && nparts == 1 && ntiles >= kStreamMinTiles && ntiles <= (1ll << 31) - 1 && (nrows & 1) == 0 &&
+    if (nparts == 1 && ntiles >= kStreamMinTiles && ntiles <= (1ll << 31) - 1 && (nrows & 1) == 0 &&
         (in_fstride & 1) == 0 && aligned16(in)) {
       const unsigned grid = unsigned(ntiles < kStreamMaxWorkgroups ? ntiles : kStreamMaxWorkgroups);
       hipLaunchKernelGGL((irfft_stream_kernel<K>), dim3(grid), dim3(256), fft_tile_lds_bytes(K, P), s, in, out, map, nrows,
@@ -206,12 +246,8 @@ hipError_t launch_irfft_k(bool rows_fast, const float2* in, float* out, const Ro
   }
   FftPlan pl = plan_fft(K, nrows);
   dim3 grid((unsigned)cdiv(nrows, 2 * pl.P));
-  if (rows_fast)
-    hipLaunchKernelGGL((irfft_kernel<K, true>), grid, dim3(pl.NT), pl.lds, s, in, out, map, nrows, in_fstride,
-                       pl.P, scale, bias, bias_div, relu, nparts, part_stride);
-  else
-    hipLaunchKernelGGL((irfft_kernel<K, false>), grid, dim3(pl.NT), pl.lds, s, in, out, map, nrows, in_fstride,
-                       pl.P, scale, bias, bias_div, relu, nparts, part_stride);
+  hipLaunchKernelGGL((irfft_kernel<K>), grid, dim3(pl.NT), pl.lds, s, in, out, map, nrows, in_fstride, pl.P, scale, bias, bias_div,
+                     relu, nparts, part_stride);
   return hipGetLastError();
 }
 
@@ -1289,12 +1325,12 @@ circ_status circ_conv_forward(const void* w_hat, const float* x, const float* bi
   float2* yh = reinterpret_cast<float2*>(static_cast<char*>(workspace) +
                                          align_up(spectrum_elems(k, xrows) * sizeof(float2), 256));
   // X^[f][j][n][pixel]: the FFT runs down the channel axis (element stride H*W)
-  RowMap mx{(int)HW, N, 1, (long long)C_in * HW, (long long)k * HW, HW, HW % 4 == 0};
+  RowMap mx{(int)HW, N, 1, (long long)C_in * HW, (long long)k * HW, HW};
   if (launch_rfft(k, true, x, xh, mx, xrows, xrows, 1, 0, 0, 1.0f, 0, s) != hipSuccess) return CIRC_EHIP;
   if (launch_conv_contract(static_cast<const float2*>(w_hat), xh, yh, p, q, NF, N, H, W, Ho, Wo, r, pad, 0, stride, 1, s) !=
       hipSuccess)
     return CIRC_EHIP;
-  RowMap my{(int)HWo, N, 1, (long long)C_out * HWo, (long long)k * HWo, HWo, HWo % 4 == 0};
+  RowMap my{(int)HWo, N, 1, (long long)C_out * HWo, (long long)k * HWo, HWo};
   if (launch_irfft(k, true, yh, y, my, yrows, yrows, 1.0f, use_bias ? bias : nullptr, (long long)N * HWo,
                    (epilogue & CIRC_EPI_RELU) ? 1 : 0, s) != hipSuccess)
     return CIRC_EHIP;
@@ -1422,13 +1458,13 @@ circ_status conv_backward_impl(const void* w_hat, const float* x, const float* d
     if (e != hipSuccess) return CIRC_EHIP;
   }
   // dY^[f][i][n][pixel]: the FFT runs down the channel axis of dy
-  RowMap my{(int)HWo, N, 1, (long long)C_out * HWo, (long long)k * HWo, HWo, HWo % 4 == 0};
+  RowMap my{(int)HWo, N, 1, (long long)C_out * HWo, (long long)k * HWo, HWo};
   if (want_dw || (dx && !dx_fused)) {
     if ((hm ? launch_rfft_chan16(k, bf, dy, yh, my, yrows, yrows, s) : launch_rfft(k, true, dy, yh, my, yrows, yrows, 1, 0, 0, 1.0f, 0, s)) !=
         hipSuccess)
       return CIRC_EHIP;
   }
-  RowMap mx{(int)HW, N, 1, (long long)C_in * HW, (long long)k * HW, HW, HW % 4 == 0};
+  RowMap mx{(int)HW, N, 1, (long long)C_in * HW, (long long)k * HW, HW};
   if (dx && !dx_fused) {
     // forward contraction on the transposed, conjugated section with reflected offsets:
     // q output blocks, p input blocks, input image Ho x Wo, output image H x W, padding r-1-pad
@@ -1556,7 +1592,7 @@ hipError_t launch_rfft_half_k(int hmode, bool bf, const void* in, void* out, con
   float2* fout = static_cast<float2*>(out);
 #define CIRC_RFFT_H(MODE)                                                                                              \
   if (!launch_rfft_stream<K, MODE>(fin, fout, map, nrows, out_fstride, scale, conj, s))                                \
-  hipLaunchKernelGGL((rfft_kernel<K, false, MODE>), grid, dim3(pl.NT), pl.lds, s, fin, fout, map, nrows, out_fstride, 0ll, \
+  hipLaunchKernelGGL((rfft_kernel<K, MODE>), grid, dim3(pl.NT), pl.lds, s, fin, fout, map, nrows, out_fstride, 0ll, \
                      0ll, pl.P, scale, conj)
   if (hmode == kHalfSpectra) {
     if (bf) { CIRC_RFFT_H(kHalfSpectra | kHalfBf16); }
@@ -1592,10 +1628,10 @@ hipError_t launch_irfft_half_k(bool bf, const void* in, void* out, const RowMap&
   FftPlan pl = plan_fft(K, nrows);
   dim3 grid((unsigned)cdiv(nrows, 2 * pl.P));
   if (bf)
-    hipLaunchKernelGGL((irfft_kernel<K, false, kHalfSpectra | kHalfRows | kHalfBf16>), grid, dim3(pl.NT), pl.lds, s, fin, fout,
+    hipLaunchKernelGGL((irfft_kernel<K, kHalfSpectra | kHalfRows | kHalfBf16>), grid, dim3(pl.NT), pl.lds, s, fin, fout,
                        map, nrows, in_fstride, pl.P, scale, bias, bias_div, relu, 1, 0ll);
   else
-    hipLaunchKernelGGL((irfft_kernel<K, false, kHalfSpectra | kHalfRows>), grid, dim3(pl.NT), pl.lds, s, fin, fout, map, nrows,
+    hipLaunchKernelGGL((irfft_kernel<K, kHalfSpectra | kHalfRows>), grid, dim3(pl.NT), pl.lds, s, fin, fout, map, nrows,
                        in_fstride, pl.P, scale, bias, bias_div, relu, 1, 0ll);
   return hipGetLastError();
 }
@@ -1889,43 +1925,19 @@ circ_status fc_backward_half(bool bf, const void* w_hat, const void* x, const vo
 
 
 // ---- CONV forward with 16-bit activations (the cached weight spectra stay fp32) ----------------
-template <int K>
-hipError_t launch_rfft_chan16_k(bool bf, const void* in, float2* out, const RowMap& map, long long nrows, long long out_fstride,
-                                hipStream_t s) {
-  FftPlan pl = plan_fft(K, nrows);
-  dim3 grid((unsigned)cdiv(nrows, 2 * pl.P), 1);
-  const float* fin = static_cast<const float*>(in);
-  if (bf)
-    hipLaunchKernelGGL((rfft_kernel<K, true, kHalfRows | kHalfBf16>), grid, dim3(pl.NT), pl.lds, s, fin, out, map, nrows,
-                       out_fstride, 0ll, 0ll, pl.P, 1.0f, 0);
-  else
-    hipLaunchKernelGGL((rfft_kernel<K, true, kHalfRows>), grid, dim3(pl.NT), pl.lds, s, fin, out, map, nrows, out_fstride, 0ll,
-                       0ll, pl.P, 1.0f, 0);
-  return hipGetLastError();
-}
-template <int K>
-hipError_t launch_irfft_chan16_k(bool bf, const float2* in, void* out, const RowMap& map, long long nrows, long long in_fstride,
-                                 const float* bias, long long bias_div, int relu, hipStream_t s) {
-  FftPlan pl = plan_fft(K, nrows);
-  dim3 grid((unsigned)cdiv(nrows, 2 * pl.P));
-  float* fout = static_cast<float*>(out);
-  if (bf)
-    hipLaunchKernelGGL((irfft_kernel<K, true, kHalfRows | kHalfBf16>), grid, dim3(pl.NT), pl.lds, s, in, fout, map, nrows,
-                       in_fstride, pl.P, 1.0f, bias, bias_div, relu, 1, 0ll);
-  else
-    hipLaunchKernelGGL((irfft_kernel<K, true, kHalfRows>), grid, dim3(pl.NT), pl.lds, s, in, fout, map, nrows, in_fstride, pl.P,
-                       1.0f, bias, bias_div, relu, 1, 0ll);
-  return hipGetLastError();
-}
 hipError_t launch_rfft_chan16(int k, bool bf, const void* in, float2* out, const RowMap& map, long long nrows,
                               long long out_fstride, hipStream_t s) {
-#define CALL(KK) launch_rfft_chan16_k<KK>(bf, in, out, map, nrows, out_fstride, s)
+#define CALL(KK)                                                                              \
+  bf ? launch_rfft_chan<KK, kHalfRows | kHalfBf16>(in, out, map, nrows, out_fstride, s)       \
+     : launch_rfft_chan<KK, kHalfRows>(in, out, map, nrows, out_fstride, s)
   CIRC_DISPATCH_HALF_K(k, CALL)
 #undef CALL
 }
 hipError_t launch_irfft_chan16(int k, bool bf, const float2* in, void* out, const RowMap& map, long long nrows,
                                long long in_fstride, const float* bias, long long bias_div, int relu, hipStream_t s) {
-#define CALL(KK) launch_irfft_chan16_k<KK>(bf, in, out, map, nrows, in_fstride, bias, bias_div, relu, s)
+#define CALL(KK)                                                                                                \
+  bf ? launch_irfft_chan<KK, kHalfRows | kHalfBf16>(in, out, map, nrows, in_fstride, bias, bias_div, relu, s)   \
+     : launch_irfft_chan<KK, kHalfRows>(in, out, map, nrows, in_fstride, bias, bias_div, relu, s)
   CIRC_DISPATCH_HALF_K(k, CALL)
 #undef CALL
 }
@@ -1962,12 +1974,12 @@ circ_status conv_forward_half(bool bf, const void* w_hat, const void* x, const f
   float2* xh = static_cast<float2*>(workspace);
   float2* yh = reinterpret_cast<float2*>(static_cast<char*>(workspace) + align_up(spectrum_elems(k, xrows) * sizeof(float2), 256));
   // the three kernels of the unfused route; only the loads of x and the stores of y are 16-bit
-  RowMap mx{(int)HW, N, 1, (long long)C_in * HW, (long long)k * HW, HW, HW % 4 == 0};
+  RowMap mx{(int)HW, N, 1, (long long)C_in * HW, (long long)k * HW, HW};
   if (launch_rfft_chan16(k, bf, x, xh, mx, xrows, xrows, s) != hipSuccess) return CIRC_EHIP;
   if (launch_conv_contract(static_cast<const float2*>(w_hat), xh, yh, p, q, NF, N, H, W, Ho, Wo, r, pad, 0, stride, 1, s) !=
       hipSuccess)
     return CIRC_EHIP;
-  RowMap my{(int)HWo, N, 1, (long long)C_out * HWo, (long long)k * HWo, HWo, HWo % 4 == 0};
+  RowMap my{(int)HWo, N, 1, (long long)C_out * HWo, (long long)k * HWo, HWo};
   if (launch_irfft_chan16(k, bf, yh, y, my, yrows, yrows, use_bias ? bias : nullptr, (long long)N * HWo, relu, s) != hipSuccess)
     return CIRC_EHIP;
   return CIRC_OK;

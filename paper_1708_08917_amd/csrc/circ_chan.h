@@ -6,8 +6,8 @@
 // of the inverse are coalesced stores: the forward transform starts in registers straight from memory and the
 // inverse ends there.  Against a tile staged in LDS on both sides this saves a pass over LDS and
 // a barrier in front of the first butterfly (and the table of row addresses with its own barrier), and all
-// loads of a thread are in flight together: 21,632 rows of 96 (13x13 images) 10.8 -> @@ us forward, 11.0 ->
-// @@ us inverse; 100,352 rows of 64 (28x28) 12.4 -> @@ us forward.
+// loads of a thread are in flight together: 21,632 rows of 96 (13x13 images) 10.8 -> 8.0 us forward, 11.6 ->
+// 9.0 us inverse; 100,352 rows of 64 (28x28) 12.4 -> 11.2 us forward (52 MB: 4.7 TB/s, a large copy reaches 5.2).
 //
 // A column is two pixels (rows 2u, 2u + 1) packed into one complex sequence.  PAIR: the image has an even
 // number of pixels, so that a column's two values are one aligned access.
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(512) void rfft_chan_kernel(const void* __restrict__
   extern __shared__ __attribute__((aligned(16))) float2 chan_z[];
   const int PP = P + 1, lgP = __ffs(P) - 1, tid = threadIdx.x, col = tid & (P - 1), n2 = tid >> lgP;
   const long long t0 = (long long)blockIdx.x * 2 * P, rid = t0 + 2 * col;
-  const long long e0 = row_base(map, min(rid, nrows - 1)) + n2 * map.es;
+  const long long e0 = row_base(map, min(rid, nrows - (PAIR ? 2 : 1))) + n2 * map.es;
   const long long e1 = PAIR ? e0 + 1 : row_base(map, min(rid + 1, nrows - 1)) + n2 * map.es;   // (rows past the end repeat the last one)
   const long long step = R2 * map.es;
   float re[R1], im[R1];
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(512) void irfft_chan_kernel(const float2* __restric
     const int f = R2 * n1 + n2;
     const long long o = (long long)(2 * f <= K ? f : K - f) * in_fstride;
     if constexpr (SPAIR) {
-      y[n1] = *reinterpret_cast<const float4*>(in + o + (PAIR ? r0 : min(rid, nrows - 2)));
+      y[n1] = *reinterpret_cast<const float4*>(in + o + min(rid, nrows - 2));
     } else {
       const float2 a = in[o + r0], b = in[o + r1];
       y[n1] = make_float4(a.x, a.y, b.x, b.y);

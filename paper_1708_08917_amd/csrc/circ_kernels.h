@@ -143,11 +143,10 @@ __device__ __forceinline__ void rfft_store_tile(const float2* z, int P, int lgP,
 // Forward real FFT of rows.  Block b handles rows [2*P*b, 2*P*(b+1)); out[f*fstride + rid]
 // holds bin f (0..K/2) of row rid, scaled by `scale`, conjugated if `conj`.
 // blockIdx.y selects one of several independent grids (weight precompute for CONV).
-// ROWS_FAST: consecutive rows are adjacent in memory (CONV, NCHW: the FFT axis is the
-// channel axis and pixels are contiguous) — lanes then run along rows when loading.
+// Rows are contiguous (images, whose rows run down the channel axis: circ_chan.h).
 // HMODE (see kHalfRows / kHalfSpectra / kHalfBf16): `in` then points to 16-bit rows and / or `out` to 16-bit pairs;
 // offsets and strides keep their meaning in elements.  K >= 4 only.
-template <int K, bool ROWS_FAST, int HMODE = 0>
+template <int K, int HMODE = 0>
 __global__ void rfft_kernel(const float* __restrict__ in, float2* __restrict__ out, RowMap map,
                             long long nrows, long long out_fstride, long long in_gstride,
                             long long out_gstride, int P, float scale, int conj) {
@@ -162,60 +161,14 @@ __global__ void rfft_kernel(const float* __restrict__ in, float2* __restrict__ o
 
   TwiddleStage<K> tws;
   tws.request(tid, NT);
-  // (groups of 4 adjacent rows, below, need no table of row addresses and no barrier before their loads)
-  const bool quad_rows = ROWS_FAST && map.quad;
-  if (!quad_rows) {
-    for (int r = tid; r < 2 * P; r += NT) {
-      long long rid = t0 + r;
-      L.rbase[r] = rid < nrows ? row_base(map, rid) : -1;
-    }
-    __syncthreads();
+  for (int r = tid; r < 2 * P; r += NT) {
+    long long rid = t0 + r;
+    L.rbase[r] = rid < nrows ? row_base(map, rid) : -1;
   }
+  __syncthreads();
 
   // load: row 2u -> real part of column u, row 2u+1 -> imaginary part
-  if constexpr (ROWS_FAST) {
-    if (map.quad) {
-      // 4 rows per 16-byte load; they are the (re, im) slots of two neighbouring columns, i.e.
-      // 4 consecutive floats of the tile (8-byte aligned: two 8-byte LDS stores).  A thread keeps
-      // its group of 4 rows (NT is a multiple of the P/2 groups of a tile) and works out their
-      // address itself; its loads, one per element index, go out together.
-      const int nq = P >> 1;                       // groups of 4 rows in the tile
-      const int qd = tid & (nq - 1), nstep = NT >> (lgP - 1);
-      const long long rid = t0 + 4 * qd;
-      float2* zq = L.z + 2 * qd;
-      if (rid < nrows) {
-        const long long b = row_base(map, rid);
-#pragma unroll 8
-        for (int n = tid >> (lgP - 1); n < K; n += nstep) {
-          float4 v;
-          if constexpr (HMODE & kHalfRows) v = load_half4<(HMODE & kHalfBf16) != 0>(reinterpret_cast<const unsigned short*>(in) + b + n * map.es);
-          else v = *reinterpret_cast<const float4*>(in + b + n * map.es);
-          float2* zd = zq + n * PP;
-          zd[0] = make_float2(v.x, v.y);
-          zd[1] = make_float2(v.z, v.w);
-        }
-      } else {
-        for (int n = tid >> (lgP - 1); n < K; n += nstep) {
-          float2* zd = zq + n * PP;
-          zd[0] = make_float2(0.f, 0.f);
-          zd[1] = make_float2(0.f, 0.f);
-        }
-      }
-    } else {
-#pragma unroll 4
-      for (int idx = tid; idx < 2 * P * K; idx += NT) {
-        int row = idx & (2 * P - 1), n = idx >> (lgP + 1);
-        long long b = L.rbase[row];
-        float v = 0.f;
-        if constexpr (HMODE & kHalfRows) {
-          if (b >= 0) v = unpack_pair16<(HMODE & kHalfBf16) != 0>(reinterpret_cast<const unsigned short*>(in)[b + n * map.es]).x;
-        } else {
-          if (b >= 0) v = in[b + n * map.es];
-        }
-        lds_put(L.z, n * PP + (row >> 1), row & 1, v);
-      }
-    }
-  } else if constexpr (K >= 4 && is_pow2_c(K)) {
+  if constexpr (K >= 4 && is_pow2_c(K)) {
     // rows are contiguous (element stride 1) and 16-byte aligned: vector loads along the row.
     // One wave-load covers 64/GW rows x GW*16 contiguous bytes.  A step of one float4 along the
     // row is 8*PP words in the tile, a multiple of 8 (PP is odd), so with all 64 lanes along one
@@ -360,7 +313,7 @@ __global__ __launch_bounds__(256) void rfft_stream_kernel(const float* __restric
 // blk = rid / bias_div (the output block row / channel block of the row).
 // The spectrum may come as `nparts` partial sums (split-K GEMM), `part_stride` elements apart;
 // they are added in index order, so the result does not depend on scheduling.
-template <int K, bool ROWS_FAST, int HMODE = 0>
+template <int K, int HMODE = 0>
 __global__ void irfft_kernel(const float2* __restrict__ in, float* __restrict__ out, RowMap map,
                              long long nrows, long long in_fstride, int P, float scale,
                              const float* __restrict__ bias, long long bias_div, int relu,
@@ -471,7 +424,7 @@ __global__ void irfft_kernel(const float2* __restrict__ in, float* __restrict__ 
   fft_lds_pass2_inplace<K, true>(L.z, PP, col, t, TT);
   __syncthreads();
 
-  if constexpr (!ROWS_FAST && K >= 4 && is_pow2_c(K)) {
+  if constexpr (K >= 4 && is_pow2_c(K)) {
     // contiguous rows: float4 stores; a thread keeps its position n in the row, its row index
     // advances by NT/(K/4) per step (NT is a multiple of K/4)
     const int n = 4 * (tid % (K / 4)), rstep = NT / (K / 4);
@@ -493,7 +446,7 @@ __global__ void irfft_kernel(const float2* __restrict__ in, float* __restrict__ 
       if constexpr (HMODE & kHalfRows) store_half4<(HMODE & kHalfBf16) != 0>(reinterpret_cast<unsigned short*>(out) + b + n, v);
       else *reinterpret_cast<float4*>(out + b + n) = v;
     }
-  } else if constexpr (!ROWS_FAST && K % 4 == 0) {
+  } else if constexpr (K % 4 == 0) {
     // the same for block sizes that are not powers of two
     constexpr int Q4 = K / 4;
 #pragma unroll 2
@@ -512,40 +465,18 @@ __global__ void irfft_kernel(const float2* __restrict__ in, float* __restrict__ 
       if constexpr (HMODE & kHalfRows) store_half4<(HMODE & kHalfBf16) != 0>(reinterpret_cast<unsigned short*>(out) + b + n, v);
       else *reinterpret_cast<float4*>(out + b + n) = v;
     }
-  } else if (ROWS_FAST && map.quad) {
-    // 4 rows per 16-byte store (see the loader of rfft_kernel); a group of 4 rows lies inside
-    // one bias block
-    const int nq = P >> 1;
-#pragma unroll 4
-    for (int idx = tid; idx < nq * K; idx += NT) {
-      const int qd = idx & (nq - 1), n = idx >> (lgP - 1);
-      long long b = L.rbase[4 * qd];
-      if (b < 0) continue;
-      const float2* zs = L.z + fft_pos<K>(n) * PP + 2 * qd;
-      const float2 u0 = zs[0], u1 = zs[1];
-      float4 v = make_float4(u0.x * scale, u0.y * scale, u1.x * scale, u1.y * scale);
-      if (bias) {
-        const float bb = bias[(long long)L.rblk[4 * qd] * K + n];
-        v.x += bb; v.y += bb; v.z += bb; v.w += bb;
-      }
-      if (relu) { v.x = fmaxf(v.x, 0.f); v.y = fmaxf(v.y, 0.f); v.z = fmaxf(v.z, 0.f); v.w = fmaxf(v.w, 0.f); }
-      if constexpr (HMODE & kHalfRows) store_half4<(HMODE & kHalfBf16) != 0>(reinterpret_cast<unsigned short*>(out) + b + n * map.es, v);
-      else *reinterpret_cast<float4*>(out + b + n * map.es) = v;
-    }
   } else {
 #pragma unroll 4
     for (int idx = tid; idx < 2 * P * K; idx += NT) {
-      int row, n;
-      if (ROWS_FAST) { row = idx & (2 * P - 1); n = idx >> (lgP + 1); }
-      else { row = idx / K; n = idx % K; }
+      const int row = idx / K, n = idx % K;
       long long b = L.rbase[row];
       if (b < 0) continue;
       float v = lds_get(L.z, fft_pos<K>(n) * PP + (row >> 1), row & 1) * scale;
       if (bias) v += bias[(long long)L.rblk[row] * K + n];
       if (relu) v = fmaxf(v, 0.f);
       if constexpr (HMODE & kHalfRows)
-        reinterpret_cast<unsigned short*>(out)[b + n * map.es] = (unsigned short)(pack_pair16<(HMODE & kHalfBf16) != 0>(v, 0.f) & 0xffffu);
-      else out[b + n * map.es] = v;
+        reinterpret_cast<unsigned short*>(out)[b + n] = (unsigned short)(pack_pair16<(HMODE & kHalfBf16) != 0>(v, 0.f) & 0xffffu);
+      else out[b + n] = v;
     }
   }
 }

@@ -622,6 +622,29 @@ def test_conv_contraction(N, p, q, k, H, W, r, pad, stride):
     check(dx, O.conv_backward_dx(w, dy, H, W, pad, stride), "dx " + what)
 
 
+# ---- transforms down the channel axis: one pixel, odd images (pairs of pixels across an image boundary, an odd
+# number of rows), even images, tiles with a tail; bias of either row of a pair; 16-bit images
+@pytest.mark.parametrize("k", [2, 4, 8, 12, 96, 100, 128, 400, 512])
+@pytest.mark.parametrize("N,H,W", [(1, 1, 1), (1, 3, 3), (2, 3, 3), (3, 5, 7), (1, 2, 5), (5, 8, 6)])
+def test_channel_transforms(k, N, H, W):
+    p, q = 3, 2
+    w = (RNG.standard_normal((1, 1, p, q, k)) / np.sqrt(q * k)).astype(np.float32)
+    x = RNG.uniform(-1, 1, (N, q * k, H, W)).astype(np.float32)
+    b = (0.1 * RNG.standard_normal(p * k)).astype(np.float32)
+    what = f"channel transforms k={k} N={N} {H}x{W}"
+    check(G.gpu_conv_forward(w, x, b, True), O.conv_forward(w, x, b, True), "fwd " + what)
+    dy = RNG.uniform(-1, 1, (N, p * k, H, W)).astype(np.float32)
+    dx, dw = G.gpu_conv_backward(w, x, dy)
+    check(dx, O.conv_backward_dx(w, dy, H, W), "dx " + what)
+    check(dw, O.conv_backward_dw(x, dy, k, 1), "dw " + what)
+    if k >= 8 and k & (k - 1) == 0:
+        wh = B.circ_precompute_spectra(G.dev(w))
+        for dtype in HALF_DTYPES:
+            xt, xr = to_half(x, dtype)
+            y = B.circ_conv_forward_f16(wh, xt, G.dev(b), None, p * k, 1, 1, 0, k, B.EPI_BIAS | B.EPI_RELU)
+            check_half(y.float().cpu().numpy(), O.conv_forward(w, xr, b, True), "fwd " + what, dtype)
+
+
 # ---- stride > 1 and even filter sizes (Eq. 6 is the stride-1 case) ---------------------------
 @pytest.mark.parametrize("N,p,q,k,H,W,r,pad,stride", [
     (2, 2, 3, 8, 9, 8, 3, 1, 2), (3, 1, 2, 16, 7, 7, 3, 0, 2), (2, 4, 4, 64, 28, 28, 3, 1, 2), (2, 2, 2, 64, 13, 12, 3, 1, 3),

@@ -110,15 +110,23 @@ def _ptr(t, dtype=None):
         raise ValueError("expected a contiguous device tensor")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"expected a {dtype} tensor, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()                       # argtypes convert the integer
 
 
 def _f32(t):
     return _ptr(t, torch.float32)
 
 
+# The current stream's handle.  torch.cuda.current_stream() builds a Stream object around it first; the calls
+# below return the handle itself.
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _check(status: int, where: str):

@@ -1502,10 +1502,18 @@ circ_status conv_backward_impl(const void* w_hat, const float* x, const float* d
       // reads, not the matrix instructions, set the pace), so the small tiles win only where they
       // are fewer than 1.5 times as many: layers with at most 2 blocks on either side
       const long long t2 = cdiv(p, 2) * cdiv(q, 2), t4 = cdiv(p, 4) * cdiv(q, 4);
+      const int BRh = (dpl.BR + 1) / 2;
+      size_t lds9 = size_t(4) * (dw_plane_stride(((2 * BRh - 1) * stride + 3) * (W + 2 * pad)) + dw_plane_stride(2 * BRh * Wo)) * sizeof(float2);
+      if (lds9 < 9216) lds9 = 9216;                                // room for the sums over the four waves
       if (2 * t2 < 3 * t4 && cdiv(r * r, 16) * t2 <= 65535) {
         dim3 grid((unsigned)dpl.nparts, (unsigned)NF, (unsigned)(cdiv(r * r, 16) * t2));
         hipLaunchKernelGGL((conv_dw_lds_kernel<true>), grid, dim3(256), dpl.lds_bytes, s, yh, xh, wpart, p, q, NF, N, H, W, Ho,
                            Wo, r, pad, dpl.BR, dpl.nbands, dpl.cpb, wstride, mul_wo_b, mul_w, stride);
+      } else if (r == 3 && lds9 <= 64 * 1024) {
+        // whole groups of eight offsets and a ninth by itself; the band's rows in two equal halves
+        dim3 grid((unsigned)dpl.nparts, (unsigned)NF, (unsigned)t4);
+        hipLaunchKernelGGL(conv_dw9_kernel, grid, dim3(256), lds9, s, yh, xh, wpart, p, q, NF, N, H, W, Ho, Wo, pad,
+                           dpl.BR, dpl.nbands, dpl.cpb, wstride, mul_wo_b, mul_w, stride);
       } else {
         dim3 grid((unsigned)dpl.nparts, (unsigned)NF, (unsigned)(cdiv(r * r, 16) * t4));
         hipLaunchKernelGGL((conv_dw_lds_kernel<false>), grid, dim3(256), dpl.lds_bytes, s, yh, xh, wpart, p, q, NF, N, H, W, Ho,

@@ -420,4 +420,152 @@ __global__ __launch_bounds__(1024) void bias_grad_column_kernel(const float* __r
   }
 }
 
+// The 4 x 4 form for 3x3 filters.  Nine offsets leave 7 of the 16 groups of a matrix instruction empty above;
+// here groups 0-7 and 8-15 take the first eight offsets at two pixels, one in the upper and one in the lower half
+// of the band's rows (so that the two differ by a constant address), and the ninth offset runs by itself with
+// a pixel of its own per group: 1/2 + 1/16 instructions and LDS reads per pixel where the form above
+// has 1.  Both are what that kernel spends its time on (LDS as busy as the matrix cores, 256 -> 256 channels
+// 28x28 batch 32: 36 us, 32 us in this form; staging takes most of the rest).  The halves and the groups are added at the end, in a fixed order.
+// Dynamic LDS: 4 * (S(((2*BRh - 1)*stride + 3) * (W + 2*pad)) + S(2*BRh*Wo)) float2, BRh = ceil(BR / 2); rows of dY^ and
+// X^ past the band are zeros.
+__global__ __launch_bounds__(256) void conv_dw9_kernel(const float2* __restrict__ dyh, const float2* __restrict__ xh,
+                                                       float2* __restrict__ part, int p, int q, int NF, int Nimg, int H, int W,
+                                                       int Ho, int Wo, int pad, int BR, int nbands, int cpb, long long part_stride,
+                                                       unsigned mul_wo, unsigned mul_w, int stride) {
+  extern __shared__ float2 xs[];                  // [4 input blocks][rows_in][Wp], then [4 output blocks][2*BRh*Wo]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), f = blockIdx.y;
+  const int blk = lane >> 2, sub = lane & 3, half = blk >> 3, tap8 = blk & 7;
+  const int njt = (q + 3) / 4, jt = blockIdx.z % njt, it = blockIdx.z / njt, i0 = it * 4, j0 = jt * 4;
+  const int Wp = W + 2 * pad, BRh = (BR + 1) >> 1, hpx = BRh * Wo;
+  const int rows_in = (2 * BRh - 1) * stride + 3;
+  const int planep = dw_plane_stride(rows_in * Wp), dplane = dw_plane_stride(2 * hpx);
+  float2* dys = xs + 4 * planep;
+  const unsigned HW = unsigned(H) * unsigned(W), HWo = unsigned(Ho) * unsigned(Wo);
+  const long long npix = (long long)Nimg * HWo;
+  const float2* dyf = dyh + (long long)f * p * npix;
+  const float2* xf = xh + (long long)f * q * Nimg * HW;
+  const float2* xsl = xs + sub * planep + (half * BRh * stride + tap8 / 3) * Wp + tap8 % 3;
+  const float2* dsl = dys + sub * dplane + half * hpx;
+  const float2* xs9 = xs + sub * planep + 2 * Wp + 2;
+  const float2* ds9 = dys + sub * dplane;
+  dw_floatx4 accR[2], accI[2], acc9R, acc9I;
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    accR[e] = dw_floatx4{0.f, 0.f, 0.f, 0.f};
+    accI[e] = dw_floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  acc9R = dw_floatx4{0.f, 0.f, 0.f, 0.f};
+  acc9I = dw_floatx4{0.f, 0.f, 0.f, 0.f};
+  // the zero columns are written once; staging only ever writes the W image columns of a row
+  for (int e = tid; e < 4 * planep; e += 256) xs[e] = make_float2(0.f, 0.f);
+  const int total = Nimg * nbands;
+  const int cend = min(total, (int(blockIdx.x) + 1) * cpb);
+  for (int c = blockIdx.x * cpb; c < cend; ++c) {
+    const int n = c / nbands, band = c - n * nbands;
+    const int ho0 = band * BR, brc = min(BR, Ho - ho0), npx = brc * Wo;
+    const int plane = rows_in * W, used = ((brc - 1) * stride + 3) * W;   // staged elements, those under the band's rows
+    __syncthreads();                              // the previous chunk has been read by every wave (first pass: zeros written)
+    {
+      const int e0 = (ho0 * stride - pad) * W;
+      const float2* src[4];
+      const float2* dsrc[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        src[u] = xf + (unsigned(min(j0 + u, q - 1)) * unsigned(Nimg) + unsigned(n)) * HW;
+        dsrc[u] = dyf + unsigned(min(i0 + u, p - 1)) * unsigned(npix) + unsigned(n) * HWo + unsigned(ho0) * unsigned(Wo);
+      }
+#pragma unroll 2
+      for (int t = tid; t < plane; t += 256) {
+        const int e = e0 + t;
+        const bool in = t < used && e >= 0 && e < int(HW);
+        const int ec = min(max(e, 0), int(HW) - 1);
+        const int dst = t + int(__umulhi(unsigned(t), mul_w)) * (2 * pad) + pad;   // row*Wp + pad + column
+        float2 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = src[u][ec];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) xs[u * planep + dst] = (in && j0 + u < q) ? v[u] : make_float2(0.f, 0.f);
+      }
+#pragma unroll 2
+      for (int t = tid; t < 2 * hpx; t += 256) {
+        const int tc = min(t, npx - 1);
+        float2 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = dsrc[u][tc];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) dys[u * dplane + t] = (t < npx && i0 + u < p) ? v[u] : make_float2(0.f, 0.f);
+      }
+    }
+    __syncthreads();
+    auto mac = [](dw_floatx4& r, dw_floatx4& m, float2 dv, float2 xv) {
+      r = __builtin_amdgcn_mfma_f32_4x4x1f32(dv.x, xv.x, r, 0, 0, 0);
+      m = __builtin_amdgcn_mfma_f32_4x4x1f32(dv.y, xv.x, m, 0, 0, 0);
+      r = __builtin_amdgcn_mfma_f32_4x4x1f32(dv.y, xv.y, r, 0, 0, 0);
+      m = __builtin_amdgcn_mfma_f32_4x4x1f32(-dv.x, xv.y, m, 0, 0, 0);
+    };
+    auto tap = [&](int pix) -> int {              // staged element of output pixel pix of a half, offset (0, 0): stride*(hl*Wp + wo)
+      return stride * (pix + int(__umulhi(unsigned(pix), mul_wo)) * (Wp - Wo));
+    };
+    // eight offsets, pixels pix and hpx + pix: wave w takes w, w + 4, ..., four at a time
+    int pix = wave;
+    for (; pix + 12 < hpx; pix += 16) {
+      float2 dv[4], xv[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        dv[u] = dsl[pix + 4 * u];
+        xv[u] = xsl[tap(pix + 4 * u)];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) mac(accR[u & 1], accI[u & 1], dv[u], xv[u]);
+    }
+    for (; pix < hpx; pix += 4) mac(accR[0], accI[0], dsl[pix], xsl[tap(pix)]);
+    // the ninth offset, pixels 16 s + group
+    for (int s = wave * 16; s < npx; s += 64) {
+      const int px = min(s + blk, npx - 1);
+      float2 dv = ds9[px];
+      const float2 xv = xs9[tap(px)];
+      if (s + blk >= npx) dv = make_float2(0.f, 0.f);
+      mac(acc9R, acc9I, dv, s + blk < npx ? xv : make_float2(0.f, 0.f));
+    }
+  }
+
+  // accumulators -> LDS (the staging area is free after the barrier); the ninth offset's 16 groups are added
+  // across lanes first
+  __syncthreads();
+  float* wsum = reinterpret_cast<float*>(xs);    // [wave][value m*2 + c][lane], then [wave][value][input block] of the ninth
+  float* wsum9 = wsum + 4 * 8 * 64;
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    wsum[(wave * 8 + 2 * m + 0) * 64 + lane] = accR[0][m] + accR[1][m];
+    wsum[(wave * 8 + 2 * m + 1) * 64 + lane] = accI[0][m] + accI[1][m];
+    float a = acc9R[m], b = acc9I[m];
+#pragma unroll
+    for (int d = 4; d < 64; d <<= 1) {
+      a += __shfl_xor(a, d);
+      b += __shfl_xor(b, d);
+    }
+    if (lane < 4) {
+      wsum9[(wave * 8 + 2 * m + 0) * 4 + lane] = a;
+      wsum9[(wave * 8 + 2 * m + 1) * 4 + lane] = b;
+    }
+  }
+  __syncthreads();
+  const long long rows = 9ll * p * q;
+  float* out = reinterpret_cast<float*>(part + (long long)blockIdx.x * part_stride + (long long)f * rows);
+  // 9 offsets x 8 values x 4 input blocks
+  for (int v = tid; v < 9 * 32; v += 256) {
+    const int jj = v & 3, e = (v >> 2) & 7, g = v >> 5, i = i0 + (e >> 1), j = j0 + jj;
+    if (i >= p || j >= q) continue;
+    float t = 0.f;
+    if (g < 8) {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) t += wsum[(w * 8 + e) * 64 + g * 4 + jj] + wsum[(w * 8 + e) * 64 + (g + 8) * 4 + jj];
+    } else {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) t += wsum9[(w * 8 + e) * 4 + jj];
+    }
+    out[2 * (((long long)g * p + i) * q + j) + (e & 1)] = t;
+  }
+}
+
 }  // namespace circ

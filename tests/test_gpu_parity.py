@@ -645,6 +645,20 @@ def test_channel_transforms(k, N, H, W):
             check_half(y.float().cpu().numpy(), O.conv_forward(w, xr, b, True), "fwd " + what, dtype)
 
 
+# ---- weight gradient of 3x3 filters: bands of an odd and an even number of rows, a short last band, one row, fewer
+# pixels than groups, strides, no padding; tiles of 4 channel blocks with a remainder on either side
+@pytest.mark.parametrize("N,p,q,k,H,W,pad,stride", [
+    (1, 4, 4, 8, 3, 3, 0, 1), (2, 4, 3, 8, 3, 9, 1, 1), (3, 5, 3, 8, 13, 13, 1, 1), (2, 3, 9, 4, 14, 28, 1, 1), (5, 4, 4, 16, 45, 41, 0, 1),
+    (2, 7, 4, 8, 30, 30, 1, 2), (33, 4, 4, 8, 5, 7, 2, 1), (1, 4, 4, 4, 4, 260, 1, 1), (2, 3, 3, 4, 100, 60, 1, 3),
+])
+def test_conv_dw_3x3(N, p, q, k, H, W, pad, stride):
+    w = (RNG.standard_normal((3, 3, p, q, k)) / np.sqrt(9 * q * k)).astype(np.float32)
+    x = RNG.uniform(-1, 1, (N, q * k, H, W)).astype(np.float32)
+    dy = RNG.uniform(-1, 1, (N, p * k, O.conv_out_size(H, 3, pad, stride), O.conv_out_size(W, 3, pad, stride))).astype(np.float32)
+    _, dw = G.gpu_conv_backward(w, x, dy, pad, need_dx=False, stride=stride)
+    check(dw, O.conv_backward_dw(x, dy, k, 3, pad, stride), f"dw 3x3 N={N} {p}x{q} k={k} {H}x{W} pad={pad} stride={stride}")
+
+
 # ---- stride > 1 and even filter sizes (Eq. 6 is the stride-1 case) ---------------------------
 @pytest.mark.parametrize("N,p,q,k,H,W,r,pad,stride", [
     (2, 2, 3, 8, 9, 8, 3, 1, 2), (3, 1, 2, 16, 7, 7, 3, 0, 2), (2, 4, 4, 64, 28, 28, 3, 1, 2), (2, 2, 2, 64, 13, 12, 3, 1, 3),

@@ -308,6 +308,32 @@ hipError_t launch_rfft(int k, bool rows_fast, const float* in, float2* out, cons
 #undef CALL
 }
 
+// Whether the transform of nrows contiguous rows takes the streaming form, which has the chip to itself.
+inline bool rfft_streams(int k, long long nrows) {
+  return is_pow2(k) && k >= 32 && k <= 256 && cdiv(nrows, 2 * (4096 / k)) >= kStreamMinTiles;
+}
+// Two transforms of contiguous rows, in one launch where neither fills the chip by itself.
+template <int K, int HMODE>
+hipError_t launch_rfft_pair_k(const RfftJob& a, const RfftJob& b, hipStream_t s) {
+  const FftPlan pl = plan_fft(K, a.nrows + b.nrows);
+  const unsigned na = (unsigned)cdiv(a.nrows, 2 * pl.P), nb = (unsigned)cdiv(b.nrows, 2 * pl.P);
+  hipLaunchKernelGGL((rfft_pair_kernel<K, HMODE>), dim3(na + nb), dim3(pl.NT), pl.lds, s, a, b, na, pl.P);
+  return hipGetLastError();
+}
+hipError_t launch_rfft_pair(int k, const RfftJob& a, const RfftJob& b, hipStream_t s) {
+  if (!rfft_streams(k, a.nrows) && !rfft_streams(k, b.nrows)) {
+#define CALL(KK) launch_rfft_pair_k<KK, 0>(a, b, s)
+    CIRC_DISPATCH_MIXED_K(k, CALL)
+    if (radix2_k(k)) CIRC_DISPATCH_K(k, CALL)
+#undef CALL
+  }
+  for (const RfftJob* j : {&a, &b})
+    if (const hipError_t e = launch_rfft(k, false, static_cast<const float*>(j->in), static_cast<float2*>(j->out), j->map, j->nrows,
+                                         j->out_fstride, 1, 0, 0, 1.0f, 0, s); e != hipSuccess)
+      return e;
+  return hipSuccess;
+}
+
 hipError_t launch_irfft(int k, bool rows_fast, const float2* in, float* out, const RowMap& map, long long nrows,
                         long long in_fstride, float scale, const float* bias, long long bias_div, int relu,
                         hipStream_t s, int nparts = 1, long long part_stride = 0) {
@@ -1022,17 +1048,13 @@ circ_status fc_backward_impl(const void* w_hat, const float* x, const float* dy,
   if (want_dw) {
     // dW^[f][i][j] = sum_b dY^[f][i][b] conj(X^[f][b][j]); X^ is batch-major, dY^ is [f][i][b] for
     // the tiled GEMM (shared with backward-data above) and batch-major [f][b][i] otherwise
-    if (dw_shares_dy) {
-      if (!have_dyh) {
-        RowMap mdy{batch, p, (long long)p * k, (long long)k, 0, 1};
-        if (launch_rfft(k, false, dy, bufy, mdy, yrows, yfs, 1, 0, 0, 1.0f, 0, s) != hipSuccess) return CIRC_EHIP;
-      }
-    } else {
-      RowMap mdy{p, batch, (long long)k, (long long)p * k, 0, 1};
-      if (launch_rfft(k, false, dy, bufy, mdy, yrows, yfs, 1, 0, 0, 1.0f, 0, s) != hipSuccess) return CIRC_EHIP;
+    const RowMap mdy = dw_shares_dy ? RowMap{batch, p, (long long)p * k, (long long)k, 0, 1} : RowMap{p, batch, (long long)k, (long long)p * k, 0, 1};
+    const RowMap mx{q, batch, (long long)k, (long long)q * k, 0, 1};
+    if (dw_shares_dy && have_dyh) {
+      if (launch_rfft(k, false, x, bufx, mx, xrows, xfs, 1, 0, 0, 1.0f, 0, s) != hipSuccess) return CIRC_EHIP;
+    } else if (launch_rfft_pair(k, RfftJob{dy, bufy, mdy, yrows, yfs}, RfftJob{x, bufx, mx, xrows, xfs}, s) != hipSuccess) {
+      return CIRC_EHIP;
     }
-    RowMap mx{q, batch, (long long)k, (long long)q * k, 0, 1};
-    if (launch_rfft(k, false, x, bufx, mx, xrows, xfs, 1, 0, 0, 1.0f, 0, s) != hipSuccess) return CIRC_EHIP;
     // the reduction over the batch is cut into slices; the IFFT adds the partial spectra in order
     const long long wpart = (long long)(align_up(spectrum_elems(k, (long long)p * q) * sizeof(float2), 256) / sizeof(float2));
     if (launch_cgemm(bufy, bufx, bufw, k, p, q, batch, yfs, xfs, wfs, true, s, ksplit, wpart, dw_shares_dy) != hipSuccess)
@@ -1663,6 +1685,20 @@ hipError_t launch_rfft_half(int k, int hmode, bool bf, const void* in, void* out
 #undef CALL
 }
 
+// (16-bit rows and spectra)
+hipError_t launch_rfft_pair_half(int k, bool bf, const RfftJob& a, const RfftJob& b, hipStream_t s) {
+  constexpr int HM = kHalfSpectra | kHalfRows;
+  if (!rfft_streams(k, a.nrows) && !rfft_streams(k, b.nrows)) {
+#define CALL(KK) bf ? launch_rfft_pair_k<KK, HM | kHalfBf16>(a, b, s) : launch_rfft_pair_k<KK, HM>(a, b, s)
+    CIRC_DISPATCH_HALF_K(k, CALL)
+#undef CALL
+  }
+  for (const RfftJob* j : {&a, &b})
+    if (const hipError_t e = launch_rfft_half(k, HM, bf, j->in, j->out, j->map, j->nrows, j->out_fstride, 1.0f, s); e != hipSuccess)
+      return e;
+  return hipSuccess;
+}
+
 hipError_t launch_irfft_half(int k, bool bf, const void* in, void* out, const RowMap& map, long long nrows,
                              long long in_fstride, float scale, const float* bias, long long bias_div, int relu,
                              hipStream_t s) {
@@ -1874,8 +1910,10 @@ circ_status fc_backward_half(bool bf, const void* w_hat, const void* x, const vo
   const bool dx_lane = dx && use_lane_forward(q, p, k, batch, true, 2 * (xs + ys), &lane);
   const bool dx_one_launch = batch <= 2 || dx_lane || use_fused_forward(q, p, k, batch);
   RowMap myt{batch, p, (long long)p * k, (long long)k, 0, 1};
+  const RowMap mxt{batch, q, (long long)q * k, (long long)k, 0, 1};
+  const RfftJob jdy{dy, dyt, myt, yrows, yrows}, jx{x, xt, mxt, xrows, xrows};
   if (dw && dx && !dx_one_launch) {
-    if (launch_rfft_half(k, hm, bf, dy, dyt, myt, yrows, yrows, 1.0f, s) != hipSuccess) return CIRC_EHIP;
+    if (launch_rfft_pair_half(k, bf, jdy, jx, s) != hipSuccess) return CIRC_EHIP;
   }
   if (dx) {
     // backward-data = the forward route on the transposed, conjugated grid (Algorithm 2):
@@ -1909,10 +1947,8 @@ circ_status fc_backward_half(bool bf, const void* w_hat, const void* x, const vo
   if (dw) {
     // dW^[f][i][j] = sum_b dY^[f][i][b] conj(X^[f][j][b]): both operands with the batch fastest
     if (!dx || dx_one_launch) {
-      if (launch_rfft_half(k, hm, bf, dy, dyt, myt, yrows, yrows, 1.0f, s) != hipSuccess) return CIRC_EHIP;
+      if (launch_rfft_pair_half(k, bf, jdy, jx, s) != hipSuccess) return CIRC_EHIP;
     }
-    RowMap mxt{batch, q, (long long)q * k, (long long)k, 0, 1};
-    if (launch_rfft_half(k, hm, bf, x, xt, mxt, xrows, xrows, 1.0f, s) != hipSuccess) return CIRC_EHIP;
     const int ks = half_dw_slices(p, q, k, batch), klen = half_dw_slice_len(batch, ks);
     const long long ps = (long long)half_dw_part_elems(p, q, k);
     dim3 grid((unsigned)(cdiv(q, 64) * ks), (unsigned)cdiv(p, 64), (unsigned)NF);

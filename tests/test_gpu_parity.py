@@ -493,6 +493,27 @@ def test_fc_short_blocks(p, q, k, batch):
             check_half(dxh.float().cpu().numpy(), O.fc_backward_dx(wt, xr), "dx " + what, dtype)
 
 
+# ---- the two transforms in front of the weight gradient in one launch: very different row counts on the two
+# sides, tiles with a tail in the first and in the second, one row, shared and batch-major layouts of dy
+@pytest.mark.parametrize("p,q,k,batch", [(1, 40, 8, 1), (40, 1, 8, 5), (3, 17, 96, 11), (17, 2, 100, 33), (2, 9, 512, 7), (70, 5, 16, 129),
+                                         (5, 70, 64, 3)])
+def test_fc_weight_gradient_transform_pair(p, q, k, batch):
+    w, x, _ = rand_fc(p, q, k, batch, bias=False)
+    dy = RNG.uniform(-1, 1, (batch, p * k)).astype(np.float32)
+    what = f"{p}x{q} k={k} B={batch}"
+    _, dw = G.gpu_fc_backward(w, x, dy, need_dx=False)
+    check(dw, O.fc_backward_dw(x, dy, k), "dw " + what)
+    dx, dw2 = G.gpu_fc_backward(w, x, dy)
+    check(dx, O.fc_backward_dx(w, dy), "dx " + what)
+    check(dw2, O.fc_backward_dw(x, dy, k), "dw beside dx " + what)
+    if k >= 8 and k & (k - 1) == 0:
+        for dtype in HALF_DTYPES:
+            (xt, xr), (dyt, dyr) = to_half(x, dtype), to_half(dy, dtype)
+            dxh, dwh = B.circ_fc_backward_f16(B.circ_precompute_spectra_f16(G.dev(w), dtype=dtype), xt, dyt, p, q, k)
+            check_half(dwh.cpu().numpy(), O.fc_backward_dw(xr, dyr, k), "dw " + what, dtype)
+            check_half(dxh.float().cpu().numpy(), O.fc_backward_dx(w, dyr), "dx " + what, dtype)
+
+
 def test_fc_forward_bf16_large_inputs():
     """Inputs far outside the fp16 range (|x| k up to 4e7) are fine in bfloat16."""
     p, q, k, batch = 3, 4, 64, 9

@@ -311,6 +311,9 @@ __global__ __launch_bounds__((LaneShape<K, MI>::NT)) void fc_lane_kernel(const v
     wave_fence();
     float X[K];
     transform(half, X);
+    // longest blocks: unpacked weights and spectra of the two parts together would not fit the registers (192 moves
+    // between the two register files per step without this)
+    if constexpr (K == 32) __builtin_amdgcn_sched_barrier(0);
     multiply(cur, X);
   };
   load_x(xs);

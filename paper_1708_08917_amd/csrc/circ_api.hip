@@ -1255,13 +1255,16 @@ hipError_t launch_conv_contract_lds(const ConvLdsPlan& pl, const float2* what, c
 template <int IT, int JQ>
 hipError_t launch_conv_contract_j(const float2* what, const float2* xh, float2* yh, int pout, int qin, int NF, int N, int H,
                                   int W, int Ho, int Wo, int r, int pad, int flip, int stride, int dil, hipStream_t s) {
-  const dim3 grid((unsigned)cdiv((long long)N * Ho * Wo, 256), (unsigned)NF, (unsigned)cdiv(pout, IT));
+  // chunks of 256 pixels of the largest residue class, for each of the up to dil^2 classes
+  const unsigned cpc = (unsigned)cdiv((long long)N * cdiv(Ho, dil) * cdiv(Wo, dil), 256);
+  const unsigned nch = dil < Ho ? dil : Ho, ncw = dil < Wo ? dil : Wo;   // (classes past the image have no pixels)
+  const dim3 grid(cpc * nch * ncw, (unsigned)NF, (unsigned)cdiv(pout, IT));
   if (dil > 1)
     hipLaunchKernelGGL((conv_contract_kernel<IT, JQ, true>), grid, dim3(256), 0, s, what, xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r,
-                       pad, flip, stride, dil);
+                       pad, flip, stride, dil, cpc);
   else
     hipLaunchKernelGGL((conv_contract_kernel<IT, JQ, false>), grid, dim3(256), 0, s, what, xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r,
-                       pad, flip, stride, dil);
+                       pad, flip, stride, dil, cpc);
   return hipGetLastError();
 }
 hipError_t launch_conv_contract(const float2* what, const float2* xh, float2* yh, int pout, int qin, int NF, int N, int H,

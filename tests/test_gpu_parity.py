@@ -680,6 +680,20 @@ def test_conv_dw_3x3(N, p, q, k, H, W, pad, stride):
     check(dw, O.conv_backward_dw(x, dy, k, 3, pad, stride), f"dw 3x3 N={N} {p}x{q} k={k} {H}x{W} pad={pad} stride={stride}")
 
 
+# ---- backward-data of strided layers, one residue class of pixels at a time: classes without a tap (stride above
+# the filter size), stride above the image size, classes of different sizes, several chunks per class, padding
+@pytest.mark.parametrize("N,p,q,k,H,W,r,pad,stride", [
+    (2, 2, 2, 8, 7, 9, 1, 0, 3), (3, 5, 3, 4, 6, 5, 3, 1, 4), (1, 2, 2, 8, 4, 3, 3, 2, 7), (9, 1, 6, 8, 23, 21, 3, 1, 2), (2, 3, 9, 16, 11, 12, 5, 2, 3),
+    (2, 2, 1, 8, 9, 1, 3, 1, 2), (1, 9, 2, 8, 8, 40, 4, 1, 2),
+])
+def test_conv_backward_data_strided(N, p, q, k, H, W, r, pad, stride):
+    w = (RNG.standard_normal((r, r, p, q, k)) / np.sqrt(r * r * q * k)).astype(np.float32)
+    x = np.zeros((N, q * k, H, W), dtype=np.float32)
+    dy = RNG.uniform(-1, 1, (N, p * k, O.conv_out_size(H, r, pad, stride), O.conv_out_size(W, r, pad, stride))).astype(np.float32)
+    dx, _ = G.gpu_conv_backward(w, x, dy, pad, need_dw=False, stride=stride)
+    check(dx, O.conv_backward_dx(w, dy, H, W, pad, stride), f"strided dx N={N} {p}x{q} k={k} {H}x{W} r={r} pad={pad} stride={stride}")
+
+
 # ---- stride > 1 and even filter sizes (Eq. 6 is the stride-1 case) ---------------------------
 @pytest.mark.parametrize("N,p,q,k,H,W,r,pad,stride", [
     (2, 2, 3, 8, 9, 8, 3, 1, 2), (3, 1, 2, 16, 7, 7, 3, 0, 2), (2, 4, 4, 64, 28, 28, 3, 1, 2), (2, 2, 2, 64, 13, 12, 3, 1, 3),

@@ -1915,8 +1915,12 @@ circ_status fc_backward_half(bool bf, const void* w_hat, const void* x, const vo
   RowMap myt{batch, p, (long long)p * k, (long long)k, 0, 1};
   const RowMap mxt{batch, q, (long long)q * k, (long long)k, 0, 1};
   const RfftJob jdy{dy, dyt, myt, yrows, yrows}, jx{x, xt, mxt, xrows, xrows};
+  // (long runs of rows are transformed one by one, each right before its use: 16384x16384 k = 256 batch 1024 measured
+  // 1 % slower with x in front of the contraction for dx)
+  const bool paired = !rfft_streams(k, yrows) && !rfft_streams(k, xrows);
   if (dw && dx && !dx_one_launch) {
-    if (launch_rfft_pair_half(k, bf, jdy, jx, s) != hipSuccess) return CIRC_EHIP;
+    if ((paired ? launch_rfft_pair_half(k, bf, jdy, jx, s) : launch_rfft_half(k, hm, bf, dy, dyt, myt, yrows, yrows, 1.0f, s)) != hipSuccess)
+      return CIRC_EHIP;
   }
   if (dx) {
     // backward-data = the forward route on the transposed, conjugated grid (Algorithm 2):
@@ -1951,6 +1955,8 @@ circ_status fc_backward_half(bool bf, const void* w_hat, const void* x, const vo
     // dW^[f][i][j] = sum_b dY^[f][i][b] conj(X^[f][j][b]): both operands with the batch fastest
     if (!dx || dx_one_launch) {
       if (launch_rfft_pair_half(k, bf, jdy, jx, s) != hipSuccess) return CIRC_EHIP;
+    } else if (!paired) {
+      if (launch_rfft_half(k, hm, bf, x, xt, mxt, xrows, xrows, 1.0f, s) != hipSuccess) return CIRC_EHIP;
     }
     const int ks = half_dw_slices(p, q, k, batch), klen = half_dw_slice_len(batch, ks);
     const long long ps = (long long)half_dw_part_elems(p, q, k);

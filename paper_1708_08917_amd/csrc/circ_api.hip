@@ -610,7 +610,7 @@ inline LanePlan plan_lane(int p, int q, int k, int batch, size_t part_bytes) {
 // size decides: short rows and many tiles favour the one launch, long rows with large batches the
 // three kernels, whose contraction reuses operands over larger tiles.  Measured, other route -> this one:
 // 4096 -> 1000 k = 8 batch 256 27.7 -> 12.7 us, 512 x 2048 blocks of 8, batch 32: 66.5 -> 19.1 us, 4096 -> 4096
-// k = 16 batch 256 31.5 -> 20.2 us, 2112 -> 1280 k = 32 batch 700 30.0 -> 19.3 us (16-bit 33.0 -> 20.2 us); kept on the
+// k = 16 batch 256 31.5 -> 20.2 us, 2112 -> 1280 k = 32 batch 700 30.0 -> 18.2 us (16-bit 33.3 -> 18.3 us); kept on the
 // other route: 4096 -> 4096 k = 32 batch 64 8.7 us against 24.5 us, k = 16 batch 1024 with 16-bit storage 35.6
 // against 53.4 us.  Over 200 shapes of 3 to 1024 batch rows the choice costs at most 9 % against the better one.
 // Times of the other routes, fitted to measurements (us):

@@ -4,10 +4,10 @@
 // A block of K <= 32 values is short enough for one lane to hold and transform, and the fp32 matrix
 // instruction v_mfma_f32_16x16x4_f32 wants, per lane, exactly one element of a 4-deep slab of the
 // reduction: lane l supplies A(m = l % 16, k = l / 16) and B(k = l / 16, n = l % 16).  So a wave takes
-// 16 output block rows x 16 batch rows and walks over the input blocks four at a time: lane (n, kk) loads
+// 16 output block rows x 16 batch rows and walks over the input blocks four at a time: lane (n, kk) takes
 // block j = 4s + kk of batch row n (K consecutive values), transforms it, and what it then holds
-// is its B operand of every frequency - no LDS, no barrier and no exchange between lanes on the way from
-// memory to the matrix cores.  The weight operand of a step is one complex value per frequency
+// is its B operand of every frequency - no exchange between the passes of a transform, no operand rows in LDS
+// and no barrier before the end of the reduction.  The weight operand of a step is one complex value per frequency
 // and lane, from the plain spectrum sections.  Per step K real products of 16x16x4 for the two real
 // bins and the four products of each complex one: 2 + 4 (K/2 - 1) instructions of 32 cycles.
 //
@@ -17,7 +17,7 @@
 //
 // What bounds it: fp32 matrix instructions and vector instructions of a SIMD, which take turns (counters at
 // 64 x 2048 blocks of 8, batch 64: matrix cores busy 45 %, and a step measures the sum of the two whatever
-// their order in the code): 448 + 184 cycles per step at K = 8, 960 + 470 at 16, 1984 + 1480 at 32.  Hence
+// their order in the code): 448 + 184 cycles per step at K = 8, 960 + 470 at 16, 1984 + 1250 at 32.  Hence
 //  - x by 16-byte pieces along the rows and a transposition through LDS: a lane per batch row, straight
 //    from memory, costs a cache access per lane (29 per instruction; 18.2 -> 16.5 us at 125 x 512 blocks of 8,
 //    batch 256),

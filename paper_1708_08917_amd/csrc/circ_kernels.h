@@ -741,7 +741,7 @@ __global__ __launch_bounds__(256) void conv_contract_kernel(const float2* __rest
   const int dil = DIL ? dil_arg : 1;                            // (the divisions by it cost a 1x1 layer a fifth of its time)
   const unsigned cls = DIL ? blockIdx.x / cpc : 0u, chunk = blockIdx.x - cls * cpc;
   const int ncw = min(dil, Wo), ca = int(cls) / ncw, cb = int(cls) - ca * ncw;   // (classes past the image have no pixels)
-  const int Hc = (Ho - ca + dil - 1) / dil, Wc = (Wo - cb + dil - 1) / dil;   // pixels of the class along either axis
+  const int Hc = (Ho - 1 - ca) / dil + 1, Wc = (Wo - 1 - cb) / dil + 1;   // pixels of the class along either axis (any dil up to 2^31 - 1)
   const long long npix = (long long)Nimg * Hc * Wc;
   const long long lpix = (long long)chunk * 256 + threadIdx.x, opix = lpix < npix ? lpix : npix - 1;
   if (npix <= (long long)chunk * 256) return;                   // (classes differ in size; the whole workgroup leaves)

@@ -1162,3 +1162,19 @@ def test_errors_raise_through_binding():
     with pytest.raises(B.CircError) as e:
         B.circ_fc_forward(wh, xd, None, xd, 2, 2, 8, 0)
     assert e.value.status == B.CIRC_EINVAL
+
+
+# ---- backward-data with the longest strides the interface takes (a single output row and column, one pixel per
+# residue class): every pixel of dx is written, into a workspace that holds no earlier values
+@pytest.mark.parametrize("stride", [2147483000, 2147483640, 2 ** 31 - 1])
+@pytest.mark.parametrize("N,H,W,r,pad", [(1, 9, 9, 3, 1), (3, 4, 11, 4, 0)])
+def test_conv_backward_data_longest_strides(N, H, W, r, pad, stride):
+    p, q, k = 2, 3, 8
+    rng = np.random.default_rng(stride % 1000 + N)
+    w = (rng.standard_normal((r, r, p, q, k)) / np.sqrt(r * r * q * k)).astype(np.float32)
+    dy = rng.uniform(-1, 1, (N, p * k, 1, 1)).astype(np.float32)
+    nbytes = B.circ_conv_backward_workspace_bytes(N, q * k, p * k, H, W, r, stride, pad, k)
+    ws = torch.full((nbytes // 4,), float("nan"), device=G.DEV).view(torch.uint8)
+    dx, _ = B.circ_conv_backward(B.circ_precompute_spectra(G.dev(w)), None, G.dev(dy), q * k, H, W, r, stride, pad, k, need_dw=False,
+                                 workspace=ws)
+    check(dx.cpu().numpy(), O.conv_backward_dx(w, dy, H, W, pad, stride), f"dx N={N} {H}x{W} r={r} pad={pad} stride={stride}")

@@ -1255,17 +1255,23 @@ hipError_t launch_conv_contract_lds(const ConvLdsPlan& pl, const float2* what, c
 template <int IT, int JQ>
 hipError_t launch_conv_contract_j(const float2* what, const float2* xh, float2* yh, int pout, int qin, int NF, int N, int H,
                                   int W, int Ho, int Wo, int r, int pad, int flip, int stride, int dil, hipStream_t s) {
-  // chunks of 256 pixels of the largest residue class, for each of the up to dil^2 classes
+  // chunks of 256 pixels of the largest residue class, for each class that meets a tap; with more residues than taps
+  // (dil > r) as many workgroups as the image has chunks for the pixels of the other classes
   const unsigned cpc = (unsigned)cdiv((long long)N * cdiv(Ho, dil) * cdiv(Wo, dil), 256);
-  const unsigned nch = dil < Ho ? dil : Ho, ncw = dil < Wo ? dil : Wo;   // (classes past the image have no pixels)
-  const dim3 grid(cpc * nch * ncw, (unsigned)NF, (unsigned)cdiv(pout, IT));
-  if (dil > 1)
+  if (dil == 1) {
+    hipLaunchKernelGGL((conv_contract_kernel<IT, JQ, false>), dim3(cpc, (unsigned)NF, (unsigned)cdiv(pout, IT)), dim3(256), 0, s, what,
+                       xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r, pad, flip, stride, dil, cpc, 0u);
+    return hipGetLastError();
+  }
+  const long long total = (long long)cpc * tap_classes(Ho, r, dil) * tap_classes(Wo, r, dil) + (dil > r ? cdiv((long long)N * Ho * Wo, 256) : 0);
+  constexpr long long kMost = (1ll << 24) - 1;                    // a launch has fewer than 2^32 threads along x
+  for (long long first = 0; first < total; first += kMost) {
+    const dim3 grid((unsigned)(total - first < kMost ? total - first : kMost), (unsigned)NF, (unsigned)cdiv(pout, IT));
     hipLaunchKernelGGL((conv_contract_kernel<IT, JQ, true>), grid, dim3(256), 0, s, what, xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r,
-                       pad, flip, stride, dil, cpc);
-  else
-    hipLaunchKernelGGL((conv_contract_kernel<IT, JQ, false>), grid, dim3(256), 0, s, what, xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r,
-                       pad, flip, stride, dil, cpc);
-  return hipGetLastError();
+                       pad, flip, stride, dil, cpc, (unsigned)first);
+    if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 hipError_t launch_conv_contract(const float2* what, const float2* xh, float2* yh, int pout, int qin, int NF, int N, int H,
                                 int W, int Ho, int Wo, int r, int pad, int flip, int stride, int dil, hipStream_t s) {

@@ -730,17 +730,44 @@ __global__ __launch_bounds__(64) void cgemm_kernel(const float2* __restrict__ A,
 //
 // dil > 1 (stride 1): an output pixel (ho, wo) only meets the taps with ho + dh - pad and wo + dw - pad multiples of dil, the
 // same ones for all pixels of its residue class (ho mod dil, wo mod dil).  A workgroup takes pixels of one class
-// (blockIdx.x = class * cpc + chunk), for which the contraction is an undilated one over every dil-th tap: no test
+// (workgroup = class * cpc + chunk), for which the contraction is an undilated one over every dil-th tap: no test
 // or division per tap, and a quarter of the taps at dil = 2 (64 -> 128 channels 3x3 stride 2, 56x56, batch 64: backward-data
-// 204 -> 116 us).
+// 204 -> 116 us).  Only classes with a tap are walked through, at most r along either axis; with dil > r the workgroups
+// behind them write the zeros of all other pixels, so that a launch never has much more than the image's pixels.
+// Residue class number c (below tap_classes) of an axis of n output positions: the residues themselves, or, where
+// there are more of those than taps, the residue that meets tap c first (past n: a class without pixels).
+__host__ __device__ inline int tap_classes(int n, int r, int dil) { return dil < n ? (dil < r ? dil : r) : (n < r ? n : r); }
+__device__ __forceinline__ int floor_mod(int a, int m) {
+  const int v = a % m;
+  return v < 0 ? v + m : v;
+}
+__device__ __forceinline__ int tap_residue(int c, int n, int r, int pad, int dil) { return min(dil, n) <= r ? c : floor_mod(pad - c, dil); }
+
+// cpc: workgroups per class; first: workgroups of earlier launches of the same call.
 template <int IT, int JQ, bool DIL>
 __global__ __launch_bounds__(256) void conv_contract_kernel(const float2* __restrict__ What, const float2* __restrict__ Xh,
                                                             float2* __restrict__ Yh, int p, int q, int NF, int Nimg, int H,
                                                             int W, int Ho, int Wo, int r, int pad, int flip, int stride, int dil_arg,
-                                                            unsigned cpc) {
+                                                            unsigned cpc, unsigned first) {
   const int dil = DIL ? dil_arg : 1;                            // (the divisions by it cost a 1x1 layer a fifth of its time)
-  const unsigned cls = DIL ? blockIdx.x / cpc : 0u, chunk = blockIdx.x - cls * cpc;
-  const int ncw = min(dil, Wo), ca = int(cls) / ncw, cb = int(cls) - ca * ncw;   // (classes past the image have no pixels)
+  unsigned chunk = blockIdx.x;
+  int ca = 0, cb = 0;
+  if constexpr (DIL) {
+    const unsigned wg = blockIdx.x + first, cls = wg / cpc, ncb = unsigned(tap_classes(Wo, r, dil));
+    chunk = wg - cls * cpc;
+    if (cls >= unsigned(tap_classes(Ho, r, dil)) * ncb) {       // (dil > r only) pixels that meet no tap
+      const unsigned px = (wg - unsigned(tap_classes(Ho, r, dil)) * ncb * cpc) * 256u + threadIdx.x, plane = unsigned(Ho) * unsigned(Wo);
+      if (px >= unsigned(Nimg) * plane) return;
+      const unsigned img = px / plane, at = px - img * plane;
+      const int ho = int(at / unsigned(Wo)), wo = int(at) - ho * Wo, i0 = blockIdx.z * IT;
+      if (floor_mod(pad - ho, dil) < r && floor_mod(pad - wo, dil) < r) return;
+      for (int i = i0; i < min(i0 + IT, p); ++i) Yh[(((long long)blockIdx.y * p + i) * Nimg + img) * plane + at] = make_float2(0.f, 0.f);
+      return;
+    }
+    ca = tap_residue(int(cls / ncb), Ho, r, pad, dil);
+    cb = tap_residue(int(cls - cls / ncb * ncb), Wo, r, pad, dil);
+    if (ca >= Ho || cb >= Wo) return;
+  }
   const int Hc = (Ho - 1 - ca) / dil + 1, Wc = (Wo - 1 - cb) / dil + 1;   // pixels of the class along either axis (any dil up to 2^31 - 1)
   const long long npix = (long long)Nimg * Hc * Wc;
   const long long lpix = (long long)chunk * 256 + threadIdx.x, opix = lpix < npix ? lpix : npix - 1;
@@ -756,7 +783,7 @@ __global__ __launch_bounds__(256) void conv_contract_kernel(const float2* __rest
   }
   const int hc = int(unsigned(rem) / unsigned(Wc)), wc = rem - hc * Wc;
   // first tap of the class along either axis, their number, and the input pixel under the first one
-  const int mh = (pad - ca) % dil, mw = (pad - cb) % dil, dh0 = mh < 0 ? mh + dil : mh, dw0 = mw < 0 ? mw + dil : mw;
+  const int dh0 = floor_mod(pad - ca, dil), dw0 = floor_mod(pad - cb, dil);
   const int nth = dh0 < r ? (r - 1 - dh0) / dil + 1 : 0, ntw = dw0 < r ? (r - 1 - dw0) / dil + 1 : 0, nt = nth * ntw;
   const int h0 = hc * stride + (ca + dh0 - pad) / dil, w0 = wc * stride + (cb + dw0 - pad) / dil;
   const unsigned plane = unsigned(Nimg) * unsigned(H * W), img = unsigned(n) * unsigned(H * W);
@@ -789,7 +816,7 @@ __global__ __launch_bounds__(256) void conv_contract_kernel(const float2* __rest
     }
   };
   int t = 0, u = 0, v = 0, j0 = 0;
-  if (nt > 0) request(0, 0, 0);
+  if (nt > 0) request(0, 0, 0);                                 // (a residue may have none: zeros are stored below)
   while (t < nt) {
     float2 x[JQ], w[JQ][IG];
 #pragma unroll

@@ -1,0 +1,81 @@
+"""Which kernels a call launches, on the CPU: the host half of the library alone, compiled with kernel
+launches stubbed out (tests/host_dry_run/dry_launch.h notes the kernels' names and checks the launch geometry)
+and the host compiler's undefined-behaviour checks in trap mode.  Each call runs in a process of its own, so
+that a trap is a test failure."""
+import json
+import os
+import re
+import shutil
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SRC = os.path.join(ROOT, "paper_1708_08917_amd", "csrc", "circ_api.hip")
+DRY = os.path.join(ROOT, "tests", "host_dry_run", "dry_launch.h")
+HIPCC = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+
+# the compiler's registration of the (absent) device code, made to do nothing
+NO_DEVICE_CODE = """
+static void* handle;
+void** __hipRegisterFatBinary(const void* data) { return &handle; }
+void __hipUnregisterFatBinary(void** h) {}
+void __hipRegisterFunction(void) {}
+void __hipRegisterVar(void) {}
+char %s[64];
+"""
+
+CALL = textwrap.dedent(r'''
+    import ctypes, json, sys
+    L = ctypes.CDLL(sys.argv[1])
+    L.circ_dry_log.restype = ctypes.c_char_p
+    P = [ctypes.c_void_p(0x10000 + i * (1 << 36)) for i in range(6)]      # device addresses, never followed
+    for fn, args in json.loads(sys.argv[2]):
+        L.circ_dry_clear()
+        conv = {"P": lambda i: P[int(i)], "N": lambda _: None, "S": lambda _: ctypes.c_size_t(1 << 62)}
+        st = getattr(L, fn)(*[a if isinstance(a, int) else conv[a[0]](a[1:]) for a in args])
+        print(json.dumps([st, L.circ_dry_log().decode()]))
+''')
+
+
+@pytest.fixture(scope="module")
+def calls(tmp_path_factory):
+    """Runs [(function, arguments), ...]; returns [(status, [kernel, ...]), ...]."""
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not found")
+    tmp = tmp_path_factory.mktemp("dispatch")
+    obj, stub, lib, drv = (str(tmp / n) for n in ("api.o", "stub.c", "libcirc_dispatch.so", "call.py"))
+    subprocess.run([HIPCC, "--offload-host-only", "-c", "-O0", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-w", "-include", DRY,
+                    "-fsanitize=undefined", "-fsanitize-trap=undefined", "-o", obj, SRC], check=True, capture_output=True, timeout=600)
+    names = subprocess.run(["nm", "-u", obj], check=True, capture_output=True, text=True).stdout
+    with open(stub, "w") as f:
+        f.write(NO_DEVICE_CODE % re.search(r"__hip_fatbin\w*", names).group(0))
+    with open(drv, "w") as f:
+        f.write(CALL)
+    subprocess.run([HIPCC, "-shared", "-fPIC", "-w", "-x", "c", stub, "-x", "none", obj, "-o", lib], check=True, capture_output=True, timeout=600)
+
+    def run(todo):
+        out = subprocess.run([sys.executable, drv, lib, json.dumps(todo)], capture_output=True, text=True, timeout=120)
+        assert out.returncode == 0, (todo, out.returncode, out.stderr[-500:])
+        res = [json.loads(l) for l in out.stdout.splitlines()]
+        names = subprocess.run(["c++filt", "-t"], input="\n".join(log for _, log in res), check=True, capture_output=True, text=True).stdout
+        # circ_dry_kernel<&(void circ::name<...>(parameters))>, or without "void" and "<...>" for a plain kernel
+        found = [re.match(r"circ_dry_kernel<&\(?(?:void )?(?:circ::)?(.*?)\(", n).group(1) for n in names.split("\n") if n]
+        it = iter(found)
+        return [(st, [next(it) for _ in log.split("\n") if _]) for st, log in res]
+    return run
+
+
+def conv_backward(N, p, q, k, H, W, r, stride, pad, dx=True, dw=True, suffix=""):
+    return ("circ_conv_backward" + suffix, ["P0", "P1", "P2", "P3" if dx else "N", "P4" if dw else "N", N, q * k, p * k, H, W, r, stride, pad, k,
+                                            "P5", "S", "N"])
+
+
+# dx of a layer whose filter moves as far as the image is long: a residue class of pixels for every pixel
+@pytest.mark.parametrize("side", [4096, 32768])
+def test_conv_backward_data_as_many_classes_as_pixels(calls, side):
+    (st, kernels), = calls([conv_backward(1, 1, 1, 2, side, side, 3, side, 1, dw=False)])
+    assert st == 0
+    assert kernels == ["rfft_chan_kernel<2, 0, false>", "conv_contract_kernel<4, 1, true>", "irfft_chan_kernel<2, 0, true, true>"]

@@ -1178,3 +1178,20 @@ def test_conv_backward_data_longest_strides(N, H, W, r, pad, stride):
     dx, _ = B.circ_conv_backward(B.circ_precompute_spectra(G.dev(w)), None, G.dev(dy), q * k, H, W, r, stride, pad, k, need_dw=False,
                                  workspace=ws)
     check(dx.cpu().numpy(), O.conv_backward_dx(w, dy, H, W, pad, stride), f"dx N={N} {H}x{W} r={r} pad={pad} stride={stride}")
+
+
+# ---- residue classes of strided backward-data where the stride exceeds the filter: more residues than taps along one
+# axis or both, images no longer than the filter along one axis, classes of several chunks, and as many residues as pixels
+@pytest.mark.parametrize("N,p,q,k,H,W,r,pad,stride", [
+    (2, 2, 3, 8, 9, 13, 1, 0, 2), (1, 5, 2, 8, 23, 17, 3, 1, 5), (3, 2, 9, 4, 3, 19, 3, 2, 8), (2, 3, 2, 4, 21, 2, 3, 2, 4), (70, 1, 1, 4, 9, 9, 3, 0, 4),
+    (1, 2, 1, 8, 30, 29, 4, 3, 30), (1, 1, 1, 2, 4096, 4096, 3, 1, 4096),
+])
+def test_conv_backward_data_stride_above_filter(N, p, q, k, H, W, r, pad, stride):
+    rng = np.random.default_rng(N + stride)
+    w = (rng.standard_normal((r, r, p, q, k)) / np.sqrt(r * r * q * k)).astype(np.float32)
+    dy = rng.uniform(-1, 1, (N, p * k, O.conv_out_size(H, r, pad, stride), O.conv_out_size(W, r, pad, stride))).astype(np.float32)
+    nbytes = B.circ_conv_backward_workspace_bytes(N, q * k, p * k, H, W, r, stride, pad, k)
+    ws = torch.full((nbytes // 4,), float("nan"), device=G.DEV).view(torch.uint8)
+    dx, _ = B.circ_conv_backward(B.circ_precompute_spectra(G.dev(w)), None, G.dev(dy), q * k, H, W, r, stride, pad, k, need_dw=False,
+                                 workspace=ws)
+    check(dx.cpu().numpy(), O.conv_backward_dx(w, dy, H, W, pad, stride), f"dx N={N} {p}x{q} k={k} {H}x{W} r={r} pad={pad} stride={stride}")

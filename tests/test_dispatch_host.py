@@ -47,7 +47,7 @@ def calls(tmp_path_factory):
         pytest.skip("hipcc not found")
     tmp = tmp_path_factory.mktemp("dispatch")
     obj, stub, lib, drv = (str(tmp / n) for n in ("api.o", "stub.c", "libcirc_dispatch.so", "call.py"))
-    subprocess.run([HIPCC, "--offload-host-only", "-c", "-O0", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-w", "-include", DRY,
+    subprocess.run([HIPCC, "--offload-host-only", "-c", "-O0", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-w", "-DCIRC_DRY_DISPATCH", "-include", DRY,
                     "-fsanitize=undefined", "-fsanitize-trap=undefined", "-o", obj, SRC], check=True, capture_output=True, timeout=600)
     names = subprocess.run(["nm", "-u", obj], check=True, capture_output=True, text=True).stdout
     with open(stub, "w") as f:

@@ -312,7 +312,10 @@ hipError_t launch_rfft(int k, bool rows_fast, const float* in, float2* out, cons
 inline bool rfft_streams(int k, long long nrows) {
   return is_pow2(k) && k >= 32 && k <= 256 && cdiv(nrows, 2 * (4096 / k)) >= kStreamMinTiles;
 }
-// Two transforms of contiguous rows, in one launch where neither fills the chip by itself.
+// Two transforms of contiguous rows, in one launch where neither fills the chip by itself.  The gain is one launch, about
+// 3 us whatever the size: above 2^24 rows (transforms of about 0.1 ms and more) it is nothing, and the rows of the longest batches
+// together would take 2^32 threads, more than one launch can have.
+inline bool rfft_pairs(int k, long long na, long long nb) { return !rfft_streams(k, na) && !rfft_streams(k, nb) && na + nb <= (1ll << 24); }
 template <int K, int HMODE>
 hipError_t launch_rfft_pair_k(const RfftJob& a, const RfftJob& b, hipStream_t s) {
   const FftPlan pl = plan_fft(K, a.nrows + b.nrows);
@@ -321,7 +324,7 @@ hipError_t launch_rfft_pair_k(const RfftJob& a, const RfftJob& b, hipStream_t s)
   return hipGetLastError();
 }
 hipError_t launch_rfft_pair(int k, const RfftJob& a, const RfftJob& b, hipStream_t s) {
-  if (!rfft_streams(k, a.nrows) && !rfft_streams(k, b.nrows)) {
+  if (rfft_pairs(k, a.nrows, b.nrows)) {
 #define CALL(KK) launch_rfft_pair_k<KK, 0>(a, b, s)
     CIRC_DISPATCH_MIXED_K(k, CALL)
     if (radix2_k(k)) CIRC_DISPATCH_K(k, CALL)
@@ -1697,7 +1700,7 @@ hipError_t launch_rfft_half(int k, int hmode, bool bf, const void* in, void* out
 // (16-bit rows and spectra)
 hipError_t launch_rfft_pair_half(int k, bool bf, const RfftJob& a, const RfftJob& b, hipStream_t s) {
   constexpr int HM = kHalfSpectra | kHalfRows;
-  if (!rfft_streams(k, a.nrows) && !rfft_streams(k, b.nrows)) {
+  if (rfft_pairs(k, a.nrows, b.nrows)) {
 #define CALL(KK) bf ? launch_rfft_pair_k<KK, HM | kHalfBf16>(a, b, s) : launch_rfft_pair_k<KK, HM>(a, b, s)
     CIRC_DISPATCH_HALF_K(k, CALL)
 #undef CALL
@@ -1923,7 +1926,7 @@ circ_status fc_backward_half(bool bf, const void* w_hat, const void* x, const vo
   const RfftJob jdy{dy, dyt, myt, yrows, yrows}, jx{x, xt, mxt, xrows, xrows};
   // (long runs of rows are transformed one by one, each right before its use: 16384x16384 k = 256 batch 1024 measured
   // 1 % slower with x in front of the contraction for dx)
-  const bool paired = !rfft_streams(k, yrows) && !rfft_streams(k, xrows);
+  const bool paired = rfft_pairs(k, yrows, xrows);
   if (dw && dx && !dx_one_launch) {
     if ((paired ? launch_rfft_pair_half(k, bf, jdy, jx, s) : launch_rfft_half(k, hm, bf, dy, dyt, myt, yrows, yrows, 1.0f, s)) != hipSuccess)
       return CIRC_EHIP;

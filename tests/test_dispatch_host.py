@@ -79,3 +79,21 @@ def test_conv_backward_data_as_many_classes_as_pixels(calls, side):
     (st, kernels), = calls([conv_backward(1, 1, 1, 2, side, side, 3, side, 1, dw=False)])
     assert st == 0
     assert kernels == ["rfft_chan_kernel<2, 0, false>", "conv_contract_kernel<4, 1, true>", "irfft_chan_kernel<2, 0, true, true>"]
+
+
+def fc_backward(p, q, k, batch, dx=True, dw=True, suffix=""):
+    return ("circ_fc_backward" + suffix, ["P0", "P1" if dw else "N", "P2", "P3" if dx else "N", "P4" if dw else "N", p, q, k, batch, "P5", "S", "N"])
+
+
+# the two transforms in front of the weight gradient: one launch for small layers; for the longest batches, whose
+# transforms fit a launch each but not together, two (134 to 249 GB of operands and workspace)
+@pytest.mark.parametrize("call,pair", [
+    (fc_backward(40, 40, 100, 64, dx=False), True), (fc_backward(64, 64, 16, 100, dx=False, suffix="_bf16"), True),
+    (fc_backward(421, 3216, 12, 606540, dx=False), False), (fc_backward(3584, 3052, 8, 341799), False),
+    (fc_backward(3436, 1681, 8, 427551, suffix="_f16"), False), (fc_backward(1643, 625, 16, 1002776, dx=False, suffix="_bf16"), False),
+])
+def test_fc_weight_gradient_transforms_in_one_launch(calls, call, pair):
+    (st, kernels), = calls([call])
+    assert st == 0
+    assert any(n.startswith("rfft_pair_kernel") for n in kernels) == pair, kernels
+    assert sum(n.startswith("rfft_kernel") for n in kernels) == (0 if pair else 2), kernels

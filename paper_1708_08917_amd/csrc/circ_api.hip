@@ -182,34 +182,44 @@ inline int plan_chan(long long nrows) {
   while (P > 16 && cdiv(nrows, 2 * P) < 512) P >>= 1;
   return P;
 }
+// (an image of 2^30 rows of 32 passes the 2^32 threads of a launch: as many launches as it takes)
+template <class Launch>
+hipError_t launch_chan_parts(long long nwg, int nthreads, const Launch& launch) {
+  const long long most = ((1ll << 32) - 1) / nthreads;
+  for (long long first = 0; first < nwg; first += most) {
+    launch(dim3((unsigned)(nwg - first < most ? nwg - first : most)), (unsigned)first);
+    if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 template <int K, int HMODE>
 hipError_t launch_rfft_chan(const void* in, float2* out, const RowMap& map, long long nrows, long long out_fstride, hipStream_t s) {
-  const int P = plan_chan<K>(nrows);
-  const dim3 grid((unsigned)cdiv(nrows, 2 * P)), block(P * radix2_of(K));
+  const int P = plan_chan<K>(nrows), NT = P * radix2_of(K);
   const size_t lds = size_t(K) * (P + 1) * sizeof(float2);
-  if (map.n0 % 2 == 0)
-    hipLaunchKernelGGL((rfft_chan_kernel<K, HMODE, true>), grid, block, lds, s, in, out, map, nrows, out_fstride, P);
-  else
-    hipLaunchKernelGGL((rfft_chan_kernel<K, HMODE, false>), grid, block, lds, s, in, out, map, nrows, out_fstride, P);
-  return hipGetLastError();
+  return launch_chan_parts(cdiv(nrows, 2 * P), NT, [&](dim3 grid, unsigned first) {
+    if (map.n0 % 2 == 0)
+      hipLaunchKernelGGL((rfft_chan_kernel<K, HMODE, true>), grid, dim3(NT), lds, s, in, out, map, nrows, out_fstride, P, first);
+    else
+      hipLaunchKernelGGL((rfft_chan_kernel<K, HMODE, false>), grid, dim3(NT), lds, s, in, out, map, nrows, out_fstride, P, first);
+  });
 }
 template <int K, int HMODE>
 hipError_t launch_irfft_chan(const float2* in, void* out, const RowMap& map, long long nrows, long long in_fstride,
                              const float* bias, long long bias_div, int relu, hipStream_t s) {
-  const int P = plan_chan<K>(nrows);
-  const dim3 grid((unsigned)cdiv(nrows, 2 * P)), block(P * radix2_of(K));
+  const int P = plan_chan<K>(nrows), NT = P * radix2_of(K);
   const size_t lds = size_t(K) * (P + 1) * sizeof(float2);
   const bool spair = (nrows | in_fstride) % 2 == 0 && aligned16(in);
-  if (map.n0 % 2 == 0 && spair)
-    hipLaunchKernelGGL((irfft_chan_kernel<K, HMODE, true, true>), grid, block, lds, s, in, out, map, nrows, in_fstride, P, bias,
-                       bias_div, relu);
-  else if (spair)
-    hipLaunchKernelGGL((irfft_chan_kernel<K, HMODE, false, true>), grid, block, lds, s, in, out, map, nrows, in_fstride, P, bias,
-                       bias_div, relu);
-  else
-    hipLaunchKernelGGL((irfft_chan_kernel<K, HMODE, false, false>), grid, block, lds, s, in, out, map, nrows, in_fstride, P, bias,
-                       bias_div, relu);
-  return hipGetLastError();
+  return launch_chan_parts(cdiv(nrows, 2 * P), NT, [&](dim3 grid, unsigned first) {
+    if (map.n0 % 2 == 0 && spair)
+      hipLaunchKernelGGL((irfft_chan_kernel<K, HMODE, true, true>), grid, dim3(NT), lds, s, in, out, map, nrows, in_fstride, P, bias,
+                         bias_div, relu, first);
+    else if (spair)
+      hipLaunchKernelGGL((irfft_chan_kernel<K, HMODE, false, true>), grid, dim3(NT), lds, s, in, out, map, nrows, in_fstride, P, bias,
+                         bias_div, relu, first);
+    else
+      hipLaunchKernelGGL((irfft_chan_kernel<K, HMODE, false, false>), grid, dim3(NT), lds, s, in, out, map, nrows, in_fstride, P, bias,
+                         bias_div, relu, first);
+  });
 }
 
 template <int K>

@@ -10,7 +10,8 @@
 // 9.0 us inverse; 100,352 rows of 64 (28x28) 12.4 -> 11.2 us forward (52 MB: 4.7 TB/s, a large copy reaches 5.2).
 //
 // A column is two pixels (rows 2u, 2u + 1) packed into one complex sequence.  PAIR: the image has an even
-// number of pixels, so that a column's two values are one aligned access.
+// number of pixels, so that a column's two values are one aligned access.  first: workgroups of earlier launches of
+// the same transform (a launch has fewer than 2^32 threads).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -52,12 +53,12 @@ __device__ __forceinline__ void chan_pass1(float (&re)[radix1_of(K)], float (&im
 // HMODE: 0, or kHalfRows (with kHalfBf16): 16-bit images, the spectra stay fp32.
 template <int K, int HMODE, bool PAIR>
 __global__ __launch_bounds__(512) void rfft_chan_kernel(const void* __restrict__ in, float2* __restrict__ out, RowMap map,
-                                                        long long nrows, long long out_fstride, int P) {
+                                                        long long nrows, long long out_fstride, int P, unsigned first) {
   constexpr int R1 = radix1_of(K), R2 = radix2_of(K);
   constexpr bool HALF = (HMODE & kHalfRows) != 0, BF = (HMODE & kHalfBf16) != 0;
   extern __shared__ __attribute__((aligned(16))) float2 chan_z[];
   const int PP = P + 1, lgP = __ffs(P) - 1, tid = threadIdx.x, col = tid & (P - 1), n2 = tid >> lgP;
-  const long long t0 = (long long)blockIdx.x * 2 * P, rid = t0 + 2 * col;
+  const long long t0 = (long long)(blockIdx.x + first) * 2 * P, rid = t0 + 2 * col;
   const long long e0 = row_base(map, min(rid, nrows - (PAIR ? 2 : 1))) + n2 * map.es;
   const long long e1 = PAIR ? e0 + 1 : row_base(map, min(rid + 1, nrows - 1)) + n2 * map.es;   // (rows past the end repeat the last one)
   const long long step = R2 * map.es;
@@ -104,12 +105,12 @@ __global__ __launch_bounds__(512) void rfft_chan_kernel(const void* __restrict__
 template <int K, int HMODE, bool PAIR, bool SPAIR>
 __global__ __launch_bounds__(512) void irfft_chan_kernel(const float2* __restrict__ in, void* __restrict__ out, RowMap map,
                                                          long long nrows, long long in_fstride, int P, const float* __restrict__ bias,
-                                                         long long bias_div, int relu) {
+                                                         long long bias_div, int relu, unsigned first) {
   constexpr int R1 = radix1_of(K), R2 = radix2_of(K);
   constexpr bool HALF = (HMODE & kHalfRows) != 0, BF = (HMODE & kHalfBf16) != 0;
   extern __shared__ __attribute__((aligned(16))) float2 chan_z[];
   const int PP = P + 1, lgP = __ffs(P) - 1, tid = threadIdx.x, col = tid & (P - 1), n2 = tid >> lgP;
-  const long long rid = (long long)blockIdx.x * 2 * P + 2 * col;
+  const long long rid = (long long)(blockIdx.x + first) * 2 * P + 2 * col;
   const long long r0 = min(rid, nrows - 1), r1 = min(rid + 1, nrows - 1);
   // Z = Ya + i Yb on all K bins (Hermitian symmetry): bin f > K/2 comes from bin K - f
   float re[R1], im[R1];

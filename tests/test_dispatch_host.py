@@ -31,7 +31,7 @@ CALL = textwrap.dedent(r'''
     import ctypes, json, sys
     L = ctypes.CDLL(sys.argv[1])
     L.circ_dry_log.restype = ctypes.c_char_p
-    P = [ctypes.c_void_p(0x10000 + i * (1 << 36)) for i in range(6)]      # device addresses, never followed
+    P = [ctypes.c_void_p(0x10000 + i * (1 << 40)) for i in range(6)]      # device addresses, never followed
     for fn, args in json.loads(sys.argv[2]):
         L.circ_dry_clear()
         conv = {"P": lambda i: P[int(i)], "N": lambda _: None, "S": lambda _: ctypes.c_size_t(1 << 62)}
@@ -61,8 +61,8 @@ def calls(tmp_path_factory):
         assert out.returncode == 0, (todo, out.returncode, out.stderr[-500:])
         res = [json.loads(l) for l in out.stdout.splitlines()]
         names = subprocess.run(["c++filt", "-t"], input="\n".join(log for _, log in res), check=True, capture_output=True, text=True).stdout
-        # circ_dry_kernel<&(void circ::name<...>(parameters))>, or without "void" and "<...>" for a plain kernel
-        found = [re.match(r"circ_dry_kernel<&\(?(?:void )?(?:circ::)?(.*?)\(", n).group(1) for n in names.split("\n") if n]
+        # circ_dry_kernel<&(void circ::name<...>(parameters))>, circ_dry_kernel<&circ::name> for a plain kernel
+        found = [re.match(r"circ_dry_kernel<&\(?(?:void )?(?:circ::)?([^(]*?)(?:\(|>$)", n).group(1) for n in names.split("\n") if n]
         it = iter(found)
         return [(st, [next(it) for _ in log.split("\n") if _]) for st, log in res]
     return run
@@ -97,3 +97,16 @@ def test_fc_weight_gradient_transforms_in_one_launch(calls, call, pair):
     assert st == 0
     assert any(n.startswith("rfft_pair_kernel") for n in kernels) == pair, kernels
     assert sum(n.startswith("rfft_kernel") for n in kernels) == (0 if pair else 2), kernels
+
+
+def conv_forward(N, p, q, k, H, W, r, stride, pad, suffix=""):
+    return ("circ_conv_forward" + suffix, ["P0", "P1", "N", "P2", N, q * k, p * k, H, W, r, stride, pad, k, 0, "P3", "S", "N"])
+
+
+# images of more than 2^30 rows of 32 channels (217 to 242 GB with the workspace): the transform of x in two launches
+@pytest.mark.parametrize("args", [(179109, 1, 21, 32, 17, 17, 11, 17, 5), (83067, 2, 52, 32, 39, 7, 3, 1, 0)])
+def test_channel_transform_longest_images(calls, args):
+    for call in (conv_forward(*args, suffix="_f16"), conv_backward(*args, suffix="_bf16")):
+        (st, kernels), = calls([call])
+        assert st == 0
+        assert sum(n.startswith("rfft_chan_kernel") for n in kernels) > (1 if call[0].startswith("circ_conv_f") else 2), kernels

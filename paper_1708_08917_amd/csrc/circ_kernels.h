@@ -743,6 +743,30 @@ __device__ __forceinline__ int floor_mod(int a, int m) {
 }
 __device__ __forceinline__ int tap_residue(int c, int n, int r, int pad, int dil) { return min(dil, n) <= r ? c : floor_mod(pad - c, dil); }
 
+// Sums of complex products of a lane, IG groups of 4 output blocks.  The products with the real and with the
+// imaginary part of the weights are summed apart and joined once: chains of half the length, whose rounding
+// errors are smaller (one chain of both: relative error 3.0e-7 -> 3.9e-7 at 10 x 26 blocks of 16, 3x3).
+template <int IG>
+struct ContractSums {
+  floatx4 wrxr[IG], wrxi[IG], wixr[IG], wixi[IG];
+  __device__ __forceinline__ void clear() {
+#pragma unroll
+    for (int g = 0; g < IG; ++g) wrxr[g] = wrxi[g] = wixr[g] = wixi[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ __forceinline__ void add(const float2 (&w)[IG], float2 x) {
+#pragma unroll
+    for (int g = 0; g < IG; ++g) {
+      wrxr[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[g].x, x.x, wrxr[g], 0, 0, 0);
+      wrxi[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[g].x, x.y, wrxi[g], 0, 0, 0);
+      wixr[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[g].y, x.x, wixr[g], 0, 0, 0);
+      wixi[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[g].y, x.y, wixi[g], 0, 0, 0);
+    }
+  }
+  __device__ __forceinline__ float2 sum(int i) const {             // output block i of the 4 * IG
+    return make_float2(wrxr[i / 4][i % 4] - wixi[i / 4][i % 4], wrxi[i / 4][i % 4] + wixr[i / 4][i % 4]);
+  }
+};
+
 // cpc: workgroups per class; first: workgroups of earlier launches of the same call.
 template <int IT, int JQ, bool DIL>
 __global__ __launch_bounds__(256) void conv_contract_kernel(const float2* __restrict__ What, const float2* __restrict__ Xh,
@@ -792,12 +816,8 @@ __global__ __launch_bounds__(256) void conv_contract_kernel(const float2* __rest
   unsigned wi[IG];                                              // this lane's output blocks
 #pragma unroll
   for (int g = 0; g < IG; ++g) wi[g] = unsigned(min(i0 + 4 * g + int(threadIdx.x & 3), p - 1));
-  floatx4 accR[IG], accI[IG];
-#pragma unroll
-  for (int g = 0; g < IG; ++g) {
-    accR[g] = floatx4{0.f, 0.f, 0.f, 0.f};
-    accI[g] = floatx4{0.f, 0.f, 0.f, 0.f};
-  }
+  ContractSums<IG> acc;
+  acc.clear();
 
   float2 next[JQ], wnext[JQ][IG];
   bool next_in;
@@ -840,16 +860,7 @@ __global__ __launch_bounds__(256) void conv_contract_kernel(const float2* __rest
 #pragma unroll
     for (int jj = 0; jj < JQ; ++jj) {
       if (jc + jj < q) {
-#pragma unroll
-        for (int g = 0; g < IG; ++g) {
-          accR[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[jj][g].x, x[jj].x, accR[g], 0, 0, 0);
-          accI[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[jj][g].x, x[jj].y, accI[g], 0, 0, 0);
-        }
-#pragma unroll
-        for (int g = 0; g < IG; ++g) {
-          accR[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[jj][g].y, -x[jj].y, accR[g], 0, 0, 0);
-          accI[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[jj][g].y, x[jj].x, accI[g], 0, 0, 0);
-        }
+        acc.add(w[jj], x[jj]);
       }
     }
   }
@@ -857,7 +868,7 @@ __global__ __launch_bounds__(256) void conv_contract_kernel(const float2* __rest
   const int at = (ca + hc * dil) * Wo + cb + wc * dil;
 #pragma unroll
   for (int ii = 0; ii < IT; ++ii)
-    if (i0 + ii < p) Yh[(((long long)f * p + i0 + ii) * Nimg + n) * Ho * Wo + at] = make_float2(accR[ii / 4][ii % 4], accI[ii / 4][ii % 4]);
+    if (i0 + ii < p) Yh[(((long long)f * p + i0 + ii) * Nimg + n) * Ho * Wo + at] = acc.sum(ii);
 }
 
 // The same contraction with the spectra staged in LDS (undilated input).  A workgroup takes, for one
@@ -915,12 +926,8 @@ __global__ __launch_bounds__(256) void conv_contract_lds_kernel(const float2* __
     const int px = min(g0 + lane, total - 1);                   // lanes past the end take part with the last pixel
     const int g = int(__umulhi(unsigned(px), mul_px)), rem = px - g * npx, hl = int(__umulhi(unsigned(rem), mul_wo)), wo = rem - hl * Wo;
     const float2* xl = cxs + g * pl + (hl * Wp + wo) * stride;
-    floatx4 accR[IG], accI[IG];
-#pragma unroll
-    for (int h = 0; h < IG; ++h) {
-      accR[h] = floatx4{0.f, 0.f, 0.f, 0.f};
-      accI[h] = floatx4{0.f, 0.f, 0.f, 0.f};
-    }
+    ContractSums<IG> acc;
+    acc.clear();
     const float2* wt = wl;
     for (int dh = 0; dh < r; ++dh) {
       for (int dw = 0; dw < r; ++dw) {
@@ -935,18 +942,7 @@ __global__ __launch_bounds__(256) void conv_contract_lds_kernel(const float2* __
             for (int h = 0; h < IG; ++h) w[u][h] = wt[u * IT + 4 * h];
           }
 #pragma unroll
-          for (int u = 0; u < N; ++u) {
-#pragma unroll
-            for (int h = 0; h < IG; ++h) {
-              accR[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[u][h].x, x[u].x, accR[h], 0, 0, 0);
-              accI[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[u][h].x, x[u].y, accI[h], 0, 0, 0);
-            }
-#pragma unroll
-            for (int h = 0; h < IG; ++h) {
-              accR[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[u][h].y, -x[u].y, accR[h], 0, 0, 0);
-              accI[h] = __builtin_amdgcn_mfma_f32_4x4x1f32(w[u][h].y, x[u].x, accI[h], 0, 0, 0);
-            }
-          }
+          for (int u = 0; u < N; ++u) acc.add(w[u], x[u]);
           xt += N * pstride;
           wt += N * IT;
         };
@@ -961,7 +957,7 @@ __global__ __launch_bounds__(256) void conv_contract_lds_kernel(const float2* __
 #pragma unroll
       for (int ii = 0; ii < IT; ++ii)
         if (i0 + ii < p)
-          Yh[(((long long)f * p + i0 + ii) * Nimg + n) * Ho * Wo + ho * Wo + wo] = make_float2(accR[ii / 4][ii % 4], accI[ii / 4][ii % 4]);
+          Yh[(((long long)f * p + i0 + ii) * Nimg + n) * Ho * Wo + ho * Wo + wo] = acc.sum(ii);
     }
   }
 }

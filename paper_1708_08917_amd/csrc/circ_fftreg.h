@@ -187,4 +187,136 @@ struct FftReg<1, INV> {
   static __device__ __forceinline__ void run(float (&)[1], float (&)[1]) {}
 };
 
+// ---- in-register FFT of K real values, K = 2, 4, 8, 16, 32 -----------------------------------------
+// Half spectrum as K floats: comp 0: bin 0, comp 1: bin K/2, comps 2f and 2f+1: re, im of bin f.
+// Decimation in time by four: real transforms of the Q = K/4 long subsequences x[4n + m], twiddles W_K^(f m), and 4-point
+// butterflies over m, of which bin f < Q/2 gives the bins f, f + Q, K/2 - f and Q - f (the last two as conjugates); the
+// inverse is the same flow backwards.  At most two roundings by twiddles on the way of a value at K = 32 (W_8 and
+// W_32), where a half-length complex transform and its separation into even and odd parts have three and one more
+// butterfly level: root mean square error 6.3e-8 forward, 6.6e-8 inverse against 7.7e-8 and 7.8e-8 in that form and
+// 6.9e-8 and 7.2e-8 of the two-pass transform of two packed rows (K = 32; fewer additions than either).
+template <int K>
+struct RealFft {
+  static constexpr int H = K / 2, Q = K / 4;
+
+  static __device__ __forceinline__ void forward(const float (&v)[K], float (&out)[K]) {
+    if constexpr (K == 2) {
+      out[0] = v[0] + v[1];
+      out[1] = v[0] - v[1];
+    } else if constexpr (K == 4) {
+      const float a = v[0] + v[2], b = v[1] + v[3];
+      out[0] = a + b;
+      out[1] = a - b;
+      out[2] = v[0] - v[2];
+      out[3] = v[3] - v[1];
+    } else {
+      float s[4][Q], a[4][Q];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+#pragma unroll
+        for (int n = 0; n < Q; ++n) s[m][n] = v[4 * n + m];
+        RealFft<Q>::forward(s[m], a[m]);
+      }
+      const float e = a[0][0] + a[2][0], o = a[1][0] + a[3][0];
+      out[0] = e + o;
+      out[1] = e - o;
+      out[2 * Q] = a[0][0] - a[2][0];
+      out[2 * Q + 1] = a[3][0] - a[1][0];
+      // bin Q/2 of the subsequences is real, its twiddles eighth roots: bins Q/2 and Q/2 + Q
+      constexpr float r = tw_cos(1, 8);
+      const float x = r * (a[1][1] - a[3][1]), y = r * (a[1][1] + a[3][1]);
+      out[Q] = a[0][1] + x;
+      out[Q + 1] = -(a[2][1] + y);
+      out[3 * Q] = a[0][1] - x;
+      out[3 * Q + 1] = a[2][1] - y;
+      bins<1>(a, out);
+    }
+  }
+
+  // sum convention (no 1/K)
+  static __device__ __forceinline__ void inverse(const float (&in)[K], float (&v)[K]) {
+    if constexpr (K == 2) {
+      v[0] = in[0] + in[1];
+      v[1] = in[0] - in[1];
+    } else if constexpr (K == 4) {
+      const float a = in[0] + in[1], b = in[0] - in[1];
+      v[0] = fmaf(2.f, in[2], a);
+      v[2] = fmaf(-2.f, in[2], a);
+      v[1] = fmaf(-2.f, in[3], b);
+      v[3] = fmaf(2.f, in[3], b);
+    } else {
+      float s[4][Q], a[4][Q];
+      const float e = in[0] + in[1], o = in[0] - in[1];
+      a[0][0] = fmaf(2.f, in[2 * Q], e);
+      a[2][0] = fmaf(-2.f, in[2 * Q], e);
+      a[1][0] = fmaf(-2.f, in[2 * Q + 1], o);
+      a[3][0] = fmaf(2.f, in[2 * Q + 1], o);
+      constexpr float r2 = 2.f * tw_cos(1, 8);
+      const float ar = in[Q], ai = in[Q + 1], br = in[3 * Q], bi = in[3 * Q + 1];
+      a[0][1] = 2.f * (ar + br);
+      a[1][1] = r2 * ((ar - ai) - (br + bi));
+      a[2][1] = 2.f * (bi - ai);
+      a[3][1] = r2 * ((br - bi) - (ar + ai));
+      inverse_bins<1>(in, a);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        RealFft<Q>::inverse(a[m], s[m]);
+#pragma unroll
+        for (int n = 0; n < Q; ++n) v[4 * n + m] = s[m][n];
+      }
+    }
+  }
+
+ private:
+  template <int F>
+  static __device__ __forceinline__ void bins(const float (&a)[4][Q], float (&out)[K]) {
+    if constexpr (2 * F < Q) {
+      float tr[4], ti[4];
+      tr[0] = a[0][2 * F];
+      ti[0] = a[0][2 * F + 1];
+      twiddle<F, 1>(tr[1], ti[1], a[1]);
+      twiddle<F, 2>(tr[2], ti[2], a[2]);
+      twiddle<F, 3>(tr[3], ti[3], a[3]);
+      const float sr = tr[0] + tr[2], si = ti[0] + ti[2], dr = tr[0] - tr[2], di = ti[0] - ti[2];
+      const float ur = tr[1] + tr[3], ui = ti[1] + ti[3], vr = tr[1] - tr[3], vi = ti[1] - ti[3];
+      out[2 * F] = sr + ur;
+      out[2 * F + 1] = si + ui;
+      out[2 * (F + Q)] = dr + vi;
+      out[2 * (F + Q) + 1] = di - vr;
+      out[2 * (H - F)] = sr - ur;
+      out[2 * (H - F) + 1] = ui - si;
+      out[2 * (Q - F)] = dr - vi;
+      out[2 * (Q - F) + 1] = -(di + vr);
+      bins<F + 1>(a, out);
+    }
+  }
+  template <int F, int M>                              // W_K^(F M) times bin F
+  static __device__ __forceinline__ void twiddle(float& tr, float& ti, const float (&a)[Q]) {
+    constexpr float c = tw_cos(F * M, K), s = tw_sin(F * M, K);
+    tr = c * a[2 * F] + s * a[2 * F + 1];
+    ti = c * a[2 * F + 1] - s * a[2 * F];
+  }
+  template <int F>
+  static __device__ __forceinline__ void inverse_bins(const float (&in)[K], float (&a)[4][Q]) {
+    if constexpr (2 * F < Q) {
+      const float y0r = in[2 * F], y0i = in[2 * F + 1], y1r = in[2 * (F + Q)], y1i = in[2 * (F + Q) + 1];
+      const float y2r = in[2 * (H - F)], y2i = -in[2 * (H - F) + 1], y3r = in[2 * (Q - F)], y3i = -in[2 * (Q - F) + 1];
+      const float sr = y0r + y2r, si = y0i + y2i, dr = y0r - y2r, di = y0i - y2i;
+      const float ur = y1r + y3r, ui = y1i + y3i, vr = y1r - y3r, vi = y1i - y3i;
+      a[0][2 * F] = sr + ur;
+      a[0][2 * F + 1] = si + ui;
+      inverse_twiddle<F, 1>(a[1], dr - vi, di + vr);
+      inverse_twiddle<F, 2>(a[2], sr - ur, si - ui);
+      inverse_twiddle<F, 3>(a[3], dr + vi, di - vr);
+      inverse_bins<F + 1>(in, a);
+    }
+  }
+  template <int F, int M>
+  static __device__ __forceinline__ void inverse_twiddle(float (&a)[Q], float tr, float ti) {
+    constexpr float c = tw_cos(F * M, K), s = tw_sin(F * M, K);
+    a[2 * F] = c * tr - s * ti;
+    a[2 * F + 1] = c * ti + s * tr;
+  }
+};
+
 }  // namespace circ

@@ -8,8 +8,8 @@
 // block j = 4s + kk of batch row n (K consecutive values), transforms it, and what it then holds
 // is its B operand of every frequency - no exchange between the passes of a transform, no operand rows in LDS
 // and no barrier before the end of the reduction.  The weight operand of a step is one complex value per frequency
-// and lane, from the plain spectrum sections.  Per step K real products of 16x16x4 for the two real
-// bins and the four products of each complex one: 2 + 4 (K/2 - 1) instructions of 32 cycles.
+// and lane, from the plain spectrum sections.  Per step one product of 16x16x4 for each of the
+// two real bins and four for each of the K/2 - 1 complex ones: 2 + 4 (K/2 - 1) instructions of 32 cycles.
 //
 // The W waves of a workgroup own the same tile and take every W-th step of the reduction; their
 // sums meet in LDS once, at the end, added in wave order, and one thread per (block row, batch row)
@@ -17,7 +17,8 @@
 //
 // What bounds it: fp32 matrix instructions and vector instructions of a SIMD, which take turns (counters at
 // 64 x 2048 blocks of 8, batch 64: matrix cores busy 45 %, and a step measures the sum of the two whatever
-// their order in the code): 448 + 184 cycles per step at K = 8, 960 + 470 at 16, 1984 + 1250 at 32.  Hence
+// their order in the code): 448 + 184 cycles per step at K = 8, 960 + 470 at 16, 1984 + 1250 at 32 (the vector part
+// with a half-length complex transform; RealFft, circ_fftreg.h, has fewer additions: 2 to 4 % of a call).  Hence
 //  - x by 16-byte pieces along the rows and a transposition through LDS: a lane per batch row, straight
 //    from memory, costs a cache access per lane (29 per instruction; 18.2 -> 16.5 us at 125 x 512 blocks of 8,
 //    batch 256),
@@ -58,79 +59,14 @@ struct LaneShape {
   static_assert(CW >= 2 * 16 * 4, "staging buffers fit");
 };
 
-// Twice the half spectrum X[0..K/2] of the K real values v (the factor is taken out of the results
-// at the end): K/2 complex points z[n] = (v[2n], v[2n+1]), then the even / odd parts of Z and one
-// butterfly level.  comp 0: bin 0, comp 1: bin K/2, comps 2f and 2f+1: re, im of bin f.
-template <int K>
-__device__ __forceinline__ void lane_rfft(const float (&v)[K], float (&out)[K]) {
-  constexpr int H = K / 2;
-  float zr[H], zi[H];
-#pragma unroll
-  for (int n = 0; n < H; ++n) {
-    zr[n] = v[2 * n];
-    zi[n] = v[2 * n + 1];
-  }
-  FftReg<H, false>::run(zr, zi);
-  out[0] = 2.f * (zr[0] + zi[0]);
-  out[1] = 2.f * (zr[0] - zi[0]);
-  out[2 * (K / 4)] = 2.f * zr[K / 4];
-  out[2 * (K / 4) + 1] = -2.f * zi[K / 4];
-  auto level = [&](auto self, auto F) {
-    constexpr int f = decltype(F)::value, g = H - f;
-    if constexpr (f < K / 4) {
-      const float er = zr[f] + zr[g], ei = zi[f] - zi[g], dr = zr[f] - zr[g], di = zi[f] + zi[g];
-      constexpr float c = tw_cos(f, K), s = tw_sin(f, K);
-      const float tr = c * di - s * dr, ti = -c * dr - s * di;
-      out[2 * f] = er + tr;
-      out[2 * f + 1] = ei + ti;
-      out[2 * g] = er - tr;
-      out[2 * g + 1] = ti - ei;
-      self(self, std::integral_constant<int, f + 1>{});
-    }
-  };
-  level(level, std::integral_constant<int, 1>{});
-}
-
-// K real values of the Hermitian spectrum given in the order above, sum convention (no 1/K).
-template <int K>
-__device__ __forceinline__ void lane_irfft(const float (&in)[K], float (&v)[K]) {
-  constexpr int H = K / 2;
-  float zr[H], zi[H];
-  zr[0] = in[0] + in[1];
-  zi[0] = in[0] - in[1];
-  zr[K / 4] = 2.f * in[2 * (K / 4)];
-  zi[K / 4] = -2.f * in[2 * (K / 4) + 1];
-  auto level = [&](auto self, auto F) {
-    constexpr int f = decltype(F)::value, g = H - f;
-    if constexpr (f < K / 4) {
-      // E = Y[f] + conj Y[g], T = e^(2 pi i f / K) (Y[f] - conj Y[g]); Z[f] = E + iT, Z[g] = conj(E - iT)
-      const float er = in[2 * f] + in[2 * g], ei = in[2 * f + 1] - in[2 * g + 1];
-      const float dr = in[2 * f] - in[2 * g], di = in[2 * f + 1] + in[2 * g + 1];
-      constexpr float c = tw_cos(f, K), s = tw_sin(f, K);
-      const float tr = c * dr - s * di, ti = c * di + s * dr;
-      zr[f] = er - ti;
-      zi[f] = ei + tr;
-      zr[g] = er + ti;
-      zi[g] = tr - ei;
-      self(self, std::integral_constant<int, f + 1>{});
-    }
-  };
-  level(level, std::integral_constant<int, 1>{});
-  FftReg<H, true>::run(zr, zi);
-#pragma unroll
-  for (int n = 0; n < H; ++n) {
-    v[2 * n] = zr[n];
-    v[2 * n + 1] = zi[n];
-  }
-}
-
-// Inverse transform, bias and ReLU of one output block (block row io of batch row bo) from twice its spectrum.
+// Inverse transform, bias and ReLU of one output block (block row io of batch row bo) from its spectrum
+// (in the order of RealFft).
 template <int K, int HM>
 __device__ __forceinline__ void lane_store(const float (&Y)[K], const float* __restrict__ bias, void* __restrict__ yv, int p, int bo,
                                            int io, int relu) {
   float v[K];
-  lane_irfft<K>(Y, v);
-  constexpr float scale = HM != 0 ? 0.5f / float(K) : 0.5f;
+  RealFft<K>::inverse(Y, v);
+  constexpr float scale = HM != 0 ? 1.0f / float(K) : 1.0f;    // (fp32 spectra carry the 1/K)
   const long long dst = (long long)bo * ((long long)p * K) + (long long)io * K;
 #pragma unroll
   for (int u = 0; u < K / 4; ++u) {
@@ -263,14 +199,23 @@ __global__ __launch_bounds__((LaneShape<K, MI>::NT)) void fc_lane_kernel(const v
         }
       }
     }
-    lane_rfft<K>(v, X);
+    RealFft<K>::forward(v, X);
   };
 
-  lanefx4 acc[MI][K];
+  // fp32, longest blocks: the products with the imaginary part of the weights have sums of their own (acc2), joined with
+  // the others at the end: half as long chains, whose rounding errors are smaller.  The fused kernel, which this one
+  // replaces at K = 32, sums the same way: relative error against float64 1.62e-7 there, 1.70e-7 here in one chain, 1.58e-7
+  // apart (2112 -> 1280, batch 700; 0.5 us of 18 for the longer start and end).  Shorter blocks replace the three-kernel
+  // route, whose one chain is longer.
+  constexpr bool APART = K == 32 && HM == 0;
+  lanefx4 acc[MI][K], acc2[APART ? MI : 1][APART ? K : 1];
 #pragma unroll
   for (int m = 0; m < MI; ++m)
 #pragma unroll
-    for (int c = 0; c < K; ++c) acc[m][c] = lanefx4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < K; ++c) {
+      acc[m][c] = lanefx4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (APART) acc2[m][c] = lanefx4{0.f, 0.f, 0.f, 0.f};
+    }
   auto multiply = [&](const WStep& s, const float (&X)[K]) {
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
@@ -294,6 +239,12 @@ __global__ __launch_bounds__((LaneShape<K, MI>::NT)) void fc_lane_kernel(const v
           // (wr + i wi) X, or (wr - i wi) X where the section holds conjugates
           a[2 * f] = __builtin_amdgcn_mfma_f32_16x16x4f32(wr, X[2 * f], a[2 * f], 0, 0, 0);
           a[2 * f + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(wr, X[2 * f + 1], a[2 * f + 1], 0, 0, 0);
+          if constexpr (APART) {
+            lanefx4(&b)[K] = acc2[m];
+            b[2 * f] = __builtin_amdgcn_mfma_f32_16x16x4f32(wi, X[2 * f + 1], b[2 * f], 0, 0, 0);
+            b[2 * f + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(wi, X[2 * f], b[2 * f + 1], 0, 0, 0);
+            continue;
+          }
           a[2 * f] = __builtin_amdgcn_mfma_f32_16x16x4f32(wi, HM != 0 ? X[2 * f + 1] : -X[2 * f + 1], a[2 * f], 0, 0, 0);
           a[2 * f + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(wi, HM != 0 ? -X[2 * f] : X[2 * f], a[2 * f + 1], 0, 0, 0);
         }
@@ -339,6 +290,13 @@ __global__ __launch_bounds__((LaneShape<K, MI>::NT)) void fc_lane_kernel(const v
   // The sums of the waves, one tile of 16 block rows after the other.
 #pragma unroll
   for (int m = 0; m < MI; ++m) {
+    if constexpr (APART) {
+#pragma unroll
+      for (int f = 1; f < K / 2; ++f) {
+        acc[m][2 * f] -= acc2[m][2 * f];
+        acc[m][2 * f + 1] += acc2[m][2 * f + 1];
+      }
+    }
     __syncthreads();                                            // the staging buffers / the tile before have been read
     float* mine = lane_smem + wave * (K * CW) + lane * 4 + kk * 16;
 #pragma unroll

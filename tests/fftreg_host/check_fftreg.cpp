@@ -45,6 +45,34 @@ static void check_reg() {
   printf("reg %s %d %.3e\n", INV ? "inv" : "fwd", R, err / mx);
 }
 
+// half spectra of real values: comp 0: bin 0, comp 1: bin K/2, comps 2f, 2f+1: re, im of bin f
+template <int K>
+static void check_real() {
+  std::vector<double> xr(K), xi(K, 0.0), yr(K), yi(K);
+  float v[K], h[K];
+  for (int n = 0; n < K; ++n) xr[n] = v[n] = float(frand());
+  naive(K, false, xr, xi, yr, yi);
+  RealFft<K>::forward(v, h);
+  double err = fmax(fabs(h[0] - yr[0]), fabs(h[1] - yr[K / 2])), mx = 0;
+  for (int f = 1; 2 * f < K; ++f) err = fmax(err, fmax(fabs(h[2 * f] - yr[f]), fabs(h[2 * f + 1] - yi[f])));
+  for (int f = 0; f < K; ++f) mx = fmax(mx, fmax(fabs(yr[f]), fabs(yi[f])));
+  printf("real fwd %d %.3e\n", K, err / mx);
+  for (int n = 0; n < K; ++n) h[n] = float(frand());
+  for (int f = 0; f < K; ++f) {
+    const int g = 2 * f <= K ? f : K - f;
+    xr[f] = g == 0 ? h[0] : 2 * g == K ? h[1] : h[2 * g];
+    xi[f] = g == 0 || 2 * g == K ? 0.0 : (2 * f < K ? 1.0 : -1.0) * h[2 * g + 1];
+  }
+  naive(K, true, xr, xi, yr, yi);
+  RealFft<K>::inverse(h, v);
+  err = mx = 0;
+  for (int n = 0; n < K; ++n) {
+    err = fmax(err, fabs(v[n] - yr[n]));
+    mx = fmax(mx, fabs(yr[n]));
+  }
+  printf("real inv %d %.3e\n", K, err / mx);
+}
+
 template <int K, bool INV>
 static void check_two_pass() {
   constexpr int R1 = radix1_of(K), R2 = radix2_of(K);
@@ -85,6 +113,7 @@ template <int... Ks>
 static void all_two_pass() { (check_two_pass<Ks, false>(), ...); (check_two_pass<Ks, true>(), ...); }
 
 int main() {
+  check_real<2>(); check_real<4>(); check_real<8>(); check_real<16>(); check_real<32>();
   srand(12345);
   all_reg<1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 12, 15, 16, 20, 24, 25, 32>();
   all_two_pass<2, 4, 8, 16, 32, 64, 128, 256, 512, 12, 24, 48, 96, 192, 384, 20, 40, 80, 160, 320, 100, 200, 400>();

@@ -36,3 +36,10 @@ def test_two_pass_split_matches_the_definition(lines):
     assert {int(l[2]) for l in two} >= {64, 128, 256, 96, 100, 384, 400} and len(two) == 46
     for _, direction, size, err in two:
         assert float(err) < 4e-6, (direction, size, err)
+
+
+def test_real_transforms_match_the_definition(lines):
+    real = [l for l in lines if l[0] == "real"]
+    assert {int(l[2]) for l in real} == {2, 4, 8, 16, 32} and len(real) == 10
+    for _, direction, size, err in real:
+        assert float(err) < 1e-6, (direction, size, err)      # at most 16 roundings of 2^-24 on the way of a value

@@ -110,3 +110,17 @@ def test_channel_transform_longest_images(calls, args):
         (st, kernels), = calls([call])
         assert st == 0
         assert sum(n.startswith("rfft_chan_kernel") for n in kernels) > (1 if call[0].startswith("circ_conv_f") else 2), kernels
+
+
+# weight gradient of 3x3 filters: rows so long that a band is a single one (about 213 to 320 pixels at stride 1) have no
+# second half for the kernel that takes two rows at a time, and the row that pads an odd band can cost a workgroup per CU
+@pytest.mark.parametrize("args,kernel", [
+    ((2, 4, 4, 16, 28, 28, 3, 1, 1), "conv_dw9_kernel"), ((2, 4, 4, 16, 200, 200, 3, 1, 1), "conv_dw9_kernel"),
+    ((2, 4, 4, 16, 224, 224, 3, 1, 1), "conv_dw_lds_kernel<false>"), ((1, 6, 6, 16, 300, 300, 3, 1, 1), "conv_dw_lds_kernel<false>"),
+    ((2, 4, 4, 16, 300, 300, 3, 2, 1), "conv_dw_lds_kernel<false>"), ((62, 4, 4, 16, 72, 72, 3, 3, 1), "conv_dw_lds_kernel<false>"),
+    ((2, 4, 4, 16, 100, 100, 3, 1, 1), "conv_dw9_kernel"), ((2, 4, 4, 16, 56, 56, 3, 3, 1), "conv_dw9_kernel"), ((2, 4, 4, 16, 9, 60, 3, 8, 1), "conv_dw9_kernel"),
+])
+def test_conv_weight_gradient_bands(calls, args, kernel):
+    (st, kernels), = calls([conv_backward(*args, dx=False)])
+    assert st == 0
+    assert [n for n in kernels if n.startswith("conv_dw")] == [kernel]

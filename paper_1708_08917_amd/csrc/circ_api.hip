@@ -1553,12 +1553,12 @@ circ_status conv_backward_impl(const void* w_hat, const float* x, const float* d
         dim3 grid((unsigned)dpl.nparts, (unsigned)NF, (unsigned)(cdiv(r * r, 16) * t2));
         hipLaunchKernelGGL((conv_dw_lds_kernel<true>), grid, dim3(256), dpl.lds_bytes, s, yh, xh, wpart, p, q, NF, N, H, W, Ho,
                            Wo, r, pad, dpl.BR, dpl.nbands, dpl.cpb, wstride, mul_wo_b, mul_w, stride);
-      } else if (r == 3 && dpl.BR > 1 && lds9 <= ((dpl.BR & 1) && stride > 2 ? 40 * 1024 : 64 * 1024)) {
-        // Whole groups of eight offsets and a ninth by itself; the band's rows in two equal halves.  Not for bands of one row,
-        // whose second half is empty (dw of two 224x224 images, 4 x 4 blocks of 16: 104 -> 119 us).  The row
-        // that pads an odd band costs less than the kernel gains (100x100, bands of 5 rows: 341 -> 325 us, even bands
-        // of 112x112: 340 -> 283 us), but at strides above 2, where staging is most of the work, only as long as four
-        // workgroups still share a CU (stride 3, bands of 5: 72x72 107 -> 115 us, 56x56 118 -> 111 us).
+      } else if (r == 3 && dpl.BR > 1 && (dpl.BR % 2 == 0 || (stride <= 2 && lds9 <= 40 * 1024)) && (long long)BRh * Wo * dpl.cpb > 128) {
+        // Whole groups of eight offsets and a ninth by itself; the band's rows in two equal halves.  The kernel starts and
+        // ends about 0.9 us later than the other (two ninths of the sums cross the lanes), which takes more than 128 pixels
+        // per half and workgroup to win back: over 900 shapes 1.0 to 1.2 times as fast above that with even bands, 0.89 to 1.0
+        // below 64.  The row that pads an odd band costs staging, the more the larger the stride, and with more than 40 KB
+        // a workgroup per CU: 0.99 to 1.15 within these limits, down to 0.77 outside them.
         dim3 grid((unsigned)dpl.nparts, (unsigned)NF, (unsigned)t4);
         hipLaunchKernelGGL(conv_dw9_kernel, grid, dim3(256), lds9, s, yh, xh, wpart, p, q, NF, N, H, W, Ho, Wo, pad,
                            dpl.BR, dpl.nbands, dpl.cpb, wstride, mul_wo_b, mul_w, stride);

@@ -112,15 +112,17 @@ def test_channel_transform_longest_images(calls, args):
         assert sum(n.startswith("rfft_chan_kernel") for n in kernels) > (1 if call[0].startswith("circ_conv_f") else 2), kernels
 
 
-# weight gradient of 3x3 filters: rows so long that a band is a single one (about 213 to 320 pixels at stride 1) have no
-# second half for the kernel that takes two rows at a time, and the row that pads an odd band can cost a workgroup per CU
-@pytest.mark.parametrize("args,kernel", [
-    ((2, 4, 4, 16, 28, 28, 3, 1, 1), "conv_dw9_kernel"), ((2, 4, 4, 16, 200, 200, 3, 1, 1), "conv_dw9_kernel"),
-    ((2, 4, 4, 16, 224, 224, 3, 1, 1), "conv_dw_lds_kernel<false>"), ((1, 6, 6, 16, 300, 300, 3, 1, 1), "conv_dw_lds_kernel<false>"),
-    ((2, 4, 4, 16, 300, 300, 3, 2, 1), "conv_dw_lds_kernel<false>"), ((62, 4, 4, 16, 72, 72, 3, 3, 1), "conv_dw_lds_kernel<false>"),
-    ((2, 4, 4, 16, 100, 100, 3, 1, 1), "conv_dw9_kernel"), ((2, 4, 4, 16, 56, 56, 3, 3, 1), "conv_dw9_kernel"), ((2, 4, 4, 16, 9, 60, 3, 8, 1), "conv_dw9_kernel"),
+# weight gradient of 3x3 filters, bands of an image's rows per workgroup.  The kernel that takes two halves of a band at a time
+# is for even bands, and odd ones of more than one row at strides up to 2 that leave room for four workgroups per CU, with more
+# than 128 pixels per half and workgroup
+@pytest.mark.parametrize("args,halves", [
+    ((32, 4, 4, 64, 28, 28, 3, 1, 1), True), ((64, 4, 4, 64, 28, 28, 3, 2, 1), True), ((2, 4, 4, 16, 200, 200, 3, 1, 1), True),
+    ((32, 4, 4, 96, 13, 13, 3, 1, 1), False), ((64, 4, 4, 96, 13, 13, 3, 1, 1), True),       # bands of 13: one and two per workgroup
+    ((2, 4, 4, 16, 224, 224, 3, 1, 1), False), ((1, 6, 6, 16, 300, 300, 3, 1, 1), False),    # bands of one row
+    ((31, 4, 4, 16, 100, 100, 3, 1, 1), False), ((62, 4, 4, 16, 72, 72, 3, 3, 1), False),    # odd bands: 44 KB, stride 3
+    ((1, 4, 4, 64, 9, 9, 3, 1, 1), False), ((15, 2, 8, 64, 2, 2, 3, 1, 1), False),           # few pixels
 ])
-def test_conv_weight_gradient_bands(calls, args, kernel):
+def test_conv_weight_gradient_bands(calls, args, halves):
     (st, kernels), = calls([conv_backward(*args, dx=False)])
     assert st == 0
-    assert [n for n in kernels if n.startswith("conv_dw")] == [kernel]
+    assert [n for n in kernels if n.startswith("conv_dw")] == ["conv_dw9_kernel" if halves else "conv_dw_lds_kernel<false>"]

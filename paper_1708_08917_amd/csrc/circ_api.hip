@@ -1230,9 +1230,21 @@ namespace {
 // second, mostly empty pass over the input (6 x 6 blocks of 64, 26 x 26 stride 2, batch 32:
 // 66 -> 37 us).
 // G images x BR output rows per workgroup of the staged contraction; G = 0: does not apply.  Among the
-// chunks whose spectra and weights fit 48 KB, the one with the least work per CU: rounds of 64 pixels on four
-// waves, staged values, a fixed part of about 1 us (cycles below), four workgroups of a CU side by side.
+// chunks whose spectra and weights fit 48 KB (of at most 64 bands per image), the one with the least work per CU: rounds
+// of 64 pixels on four waves, staged values, a fixed part of about 1 us (cycles below), four workgroups of a CU
+// side by side (three above 40 KB, for which the estimate is low).
 struct ConvLdsPlan { int G, BR, nbands, pstride; size_t lds; };
+// Whether the best chunk is worth staging: it is if its staged values, weights included, are few against the products that
+// read them (2.4 and more each), and otherwise (strides of the filter size and more, chunks of a few pixels) only
+// where all workgroups are resident at once, where what counts is that the loads go out together.  Over 725 shapes
+// (2x2 to 7x7, strides 1 to 5) staging always costs 2.8 % on average against the better form and up to 7 times (81 x 34
+// blocks of 8, 112x10 stride 4: 460 us against 66), never 21 %; this rule 0.7 % and at most 1.35 times.
+inline bool conv_lds_pays(const ConvLdsPlan& pl, int it, int pout, int NF, int N, int W, int Wo, int r, int pad, int stride) {
+  const long long plane = ((long long)(pl.BR - 1) * stride + r) * (W + 2 * pad), taps = (long long)r * r;
+  const long long staged = pl.G * plane + taps * it, reads = (long long)pl.G * pl.BR * Wo * taps;   // per input block
+  const long long wgs = cdiv(N, pl.G) * pl.nbands * NF * cdiv(pout, it), room = 160 * 1024 / (long long)pl.lds;
+  return 12 * staged <= 5 * reads || wgs <= 256 * (room < 8 ? room : 8);
+}
 inline ConvLdsPlan plan_conv_lds(int it, int pout, int qin, int NF, int N, int W, int Ho, int Wo, int r, int pad, int stride) {
   ConvLdsPlan best{0, 0, 0, 0, 0};
   const long long Wp = (long long)W + 2 * pad, taps = (long long)r * r, wbytes = taps * qin * it * 8;
@@ -1294,7 +1306,7 @@ hipError_t launch_conv_contract(const float2* what, const float2* xh, float2* yh
   if (dil == 1 && r > 1) {
     const int it = pout > 4 ? 8 : 4;
     const ConvLdsPlan pl = plan_conv_lds(it, pout, qin, NF, N, W, Ho, Wo, r, pad, stride);
-    if (pl.G > 0)
+    if (pl.G > 0 && conv_lds_pays(pl, it, pout, NF, N, W, Wo, r, pad, stride))
       return it == 8 ? launch_conv_contract_lds<8>(pl, what, xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r, pad, flip, stride, s)
                      : launch_conv_contract_lds<4>(pl, what, xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r, pad, flip, stride, s);
   }

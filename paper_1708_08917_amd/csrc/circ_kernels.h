@@ -720,8 +720,8 @@ __global__ __launch_bounds__(64) void cgemm_kernel(const float2* __restrict__ A,
 // supplies the weight of block i0 + l % 4 and the spectrum value of its own pixel, and receives the sums
 // of its own pixel - the layout of one thread per pixel, at twice the rate of the vector ALUs (64 x 4
 // products in 8 cycles against 16) and with a 1-cache-line load in place of scalar loads of the weights.
-// Serves 1x1 filters, backward-data of strided layers (dil > 1) and images too wide for the staged kernel
-// below.  What is left is memory latency, so the (tap, group of JQ input blocks) pairs form one
+// Serves 1x1 filters, backward-data of strided layers (dil > 1) and what the staged kernel below cannot hold or does
+// not pay for (conv_lds_pays).  What is left is memory latency, so the (tap, group of JQ input blocks) pairs form one
 // sequence, and the values of the next pair are requested before the current one is multiplied.  Taps
 // outside the image read a valid address and are replaced by zeros.  Lanes past the last pixel take
 // part with the last one (a group needs all of its weights).

@@ -126,3 +126,16 @@ def test_conv_weight_gradient_bands(calls, args, halves):
     (st, kernels), = calls([conv_backward(*args, dx=False)])
     assert st == 0
     assert [n for n in kernels if n.startswith("conv_dw")] == ["conv_dw9_kernel" if halves else "conv_dw_lds_kernel<false>"]
+
+
+# CONV contraction: spectra staged in LDS where each staged value (weights included) is read more than twice on average
+# or all workgroups are resident at once, and from memory otherwise
+@pytest.mark.parametrize("args,staged", [
+    ((32, 4, 4, 96, 13, 13, 3, 1, 1), True), ((16, 5, 5, 64, 20, 20, 5, 1, 2), True), ((2, 4, 4, 96, 27, 27, 3, 3, 1), True),
+    ((10, 81, 34, 8, 112, 10, 3, 4, 2), False), ((63, 1, 1, 512, 280, 3, 3, 4, 2), False), ((19, 270, 24, 2, 40, 43, 3, 1, 2), False),
+    ((8, 2, 2, 128, 56, 56, 1, 1, 0), False),
+])
+def test_conv_contraction_staged(calls, args, staged):
+    (st, kernels), = calls([conv_forward(*args)])
+    assert st == 0
+    assert kernels[1].startswith("conv_contract_lds_kernel<" if staged else "conv_contract_kernel<"), kernels

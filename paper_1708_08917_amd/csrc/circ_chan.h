@@ -95,7 +95,9 @@ __global__ __launch_bounds__(512) void rfft_chan_kernel(const void* __restrict__
   chan_twiddles<K>(w, n2);
   chan_pass1<K, false>(re, im, w, chan_z, PP, col, n2);
   __syncthreads();
-  fft_lds_pass2_inplace<K, false>(chan_z, PP, col, n2, R2);
+  // (as fft_lds_pass2_inplace, spelled out: with that function in common the compiler gives rfft_kernel more registers,
+  // 116 instead of 94 at K = 192, which cost that kernel a wave per SIMD and a fourth of its speed)
+  fft_lds_pass2<K, false>(chan_z, PP, col, n2, R2, [&](int f, float2 v) { chan_z[fft_pos<K>(f) * PP + col] = v; });
   __syncthreads();
   rfft_store_tile<K, 0>(chan_z, P, lgP, tid, blockDim.x, t0, nrows, out, out_fstride, 1.0f, 0);
 }

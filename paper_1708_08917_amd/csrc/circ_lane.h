@@ -338,12 +338,30 @@ __global__ __launch_bounds__(256) void lane_finish_kernel(const float* __restric
 #pragma unroll
   for (int c = 0; c < K; ++c) Y[c] = src[c * 256];
   const size_t ps = size_t(gridDim.x) * (K * 256);
-#pragma unroll 4                                     // a few slices in flight: a tile has one workgroup
-  for (int s = 1; s < nparts; ++s) {
-    src += ps;
+  // A tile has one workgroup, so the loads have to overlap: U slices, 64 values, are requested before the first of them is
+  // added, then the rest in smaller groups (left to itself the compiler waits for every value at K = 32: 16 slices
+  // 35.6 us, about 8 in this form).
+  constexpr int U = 64 / K;
+  int s = 1;
+  auto add = [&](auto count) {
+    constexpr int N = decltype(count)::value;
+    float t[N][K];
 #pragma unroll
-    for (int c = 0; c < K; ++c) Y[c] += src[c * 256];
-  }
+    for (int u = 0; u < N; ++u)
+#pragma unroll
+      for (int c = 0; c < K; ++c) t[u][c] = (src + size_t(s + u) * ps)[c * 256];
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < N; ++u)
+#pragma unroll
+      for (int c = 0; c < K; ++c) Y[c] += t[u][c];
+    s += N;
+  };
+  while (s + U <= nparts) add(std::integral_constant<int, U>{});
+  if constexpr (U > 8) { if (s + 8 <= nparts) add(std::integral_constant<int, 8>{}); }
+  if constexpr (U > 4) { if (s + 4 <= nparts) add(std::integral_constant<int, 4>{}); }
+  if constexpr (U > 2) { if (s + 2 <= nparts) add(std::integral_constant<int, 2>{}); }
+  if (s < nparts) add(std::integral_constant<int, 1>{});
   lane_store<K, HM>(Y, bias, yv, p, bo, io, relu);
 }
 

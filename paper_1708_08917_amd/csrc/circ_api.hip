@@ -1564,16 +1564,19 @@ circ_status conv_backward_impl(const void* w_hat, const float* x, const float* d
       const int BRh = (dpl.BR + 1) / 2;
       size_t lds9 = size_t(4) * (dw_plane_stride(((2 * BRh - 1) * stride + 3) * (W + 2 * pad)) + dw_plane_stride(2 * BRh * Wo)) * sizeof(float2);
       if (lds9 < 9216) lds9 = 9216;                                // room for the sums over the four waves
+      const long long half_px = (long long)BRh * Wo * dpl.cpb;     // pixels of either half per workgroup
       if (2 * t2 < 3 * t4 && cdiv(r * r, 16) * t2 <= 65535) {
         dim3 grid((unsigned)dpl.nparts, (unsigned)NF, (unsigned)(cdiv(r * r, 16) * t2));
         hipLaunchKernelGGL((conv_dw_lds_kernel<true>), grid, dim3(256), dpl.lds_bytes, s, yh, xh, wpart, p, q, NF, N, H, W, Ho,
                            Wo, r, pad, dpl.BR, dpl.nbands, dpl.cpb, wstride, mul_wo_b, mul_w, stride);
-      } else if (r == 3 && dpl.BR > 1 && (dpl.BR % 2 == 0 || (stride <= 2 && lds9 <= 40 * 1024)) && (long long)BRh * Wo * dpl.cpb > 128) {
-        // Whole groups of eight offsets and a ninth by itself; the band's rows in two equal halves.  The kernel starts and
-        // ends about 0.9 us later than the other (two ninths of the sums cross the lanes), which takes more than 128 pixels
-        // per half and workgroup to win back: over 900 shapes 1.0 to 1.2 times as fast above that with even bands, 0.89 to 1.0
-        // below 64.  The row that pads an odd band costs staging, the more the larger the stride, and with more than 40 KB
-        // a workgroup per CU: 0.99 to 1.15 within these limits, down to 0.77 outside them.
+      } else if (r == 3 && dpl.BR > 1 && (dpl.BR % 2 == 0 || (stride <= 2 && lds9 <= 40 * 1024)) &&
+                 (half_px > 128 || (half_px > 64 && stride <= 2 && dpl.nparts * NF * t4 >= 1024))) {
+        // Whole groups of eight offsets and a ninth by itself; the band's rows in two equal halves.  A workgroup starts and
+        // ends about 0.9 us later than with the other kernel (two ninths of the sums cross the lanes), which takes more than
+        // 128 pixels per half to win back, half of that where there are enough workgroups to share it.  The row that pads
+        // an odd band costs staging, the more the larger the stride, and with more than 40 KB a workgroup per CU.  Over 900
+        // shapes 0.96 to 1.22 times as fast within these limits (mean of all 0.1 % off the better choice), down to
+        // 0.48 outside them.
         dim3 grid((unsigned)dpl.nparts, (unsigned)NF, (unsigned)t4);
         hipLaunchKernelGGL(conv_dw9_kernel, grid, dim3(256), lds9, s, yh, xh, wpart, p, q, NF, N, H, W, Ho, Wo, pad,
                            dpl.BR, dpl.nbands, dpl.cpb, wstride, mul_wo_b, mul_w, stride);

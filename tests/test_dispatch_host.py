@@ -114,10 +114,11 @@ def test_channel_transform_longest_images(calls, args):
 
 # weight gradient of 3x3 filters, bands of an image's rows per workgroup.  The kernel that takes two halves of a band at a time
 # is for even bands, and odd ones of more than one row at strides up to 2 that leave room for four workgroups per CU, with more
-# than 128 pixels per half and workgroup
+# than 128 pixels per half and workgroup (64 with strides up to 2 and at least 1024 workgroups)
 @pytest.mark.parametrize("args,halves", [
     ((32, 4, 4, 64, 28, 28, 3, 1, 1), True), ((64, 4, 4, 64, 28, 28, 3, 2, 1), True), ((2, 4, 4, 16, 200, 200, 3, 1, 1), True),
-    ((32, 4, 4, 96, 13, 13, 3, 1, 1), False), ((64, 4, 4, 96, 13, 13, 3, 1, 1), True),       # bands of 13: one and two per workgroup
+    ((32, 4, 4, 96, 13, 13, 3, 1, 1), True), ((16, 4, 4, 96, 13, 13, 3, 1, 1), False),       # 91 pixels, 1568 and 784 workgroups
+    ((64, 4, 4, 16, 13, 13, 3, 1, 1), True),                                                 # two bands of 91 per workgroup
     ((2, 4, 4, 16, 224, 224, 3, 1, 1), False), ((1, 6, 6, 16, 300, 300, 3, 1, 1), False),    # bands of one row
     ((31, 4, 4, 16, 100, 100, 3, 1, 1), False), ((62, 4, 4, 16, 72, 72, 3, 3, 1), False),    # odd bands: 44 KB, stride 3
     ((1, 4, 4, 64, 9, 9, 3, 1, 1), False), ((15, 2, 8, 64, 2, 2, 3, 1, 1), False),           # few pixels

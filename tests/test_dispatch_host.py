@@ -12,6 +12,8 @@ import textwrap
 
 import pytest
 
+from tests.short_block_cases import CASES
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = os.path.join(ROOT, "paper_1708_08917_amd", "csrc", "circ_api.hip")
 DRY = os.path.join(ROOT, "tests", "host_dry_run", "dry_launch.h")
@@ -140,3 +142,21 @@ def test_conv_contraction_staged(calls, args, staged):
     (st, kernels), = calls([conv_forward(*args)])
     assert st == 0
     assert kernels[1].startswith("conv_contract_lds_kernel<" if staged else "conv_contract_kernel<"), kernels
+
+
+def fc_forward(p, q, k, batch, suffix=""):
+    return ("circ_fc_forward" + suffix, ["P0", "P1", "N", "P2", p, q, k, batch, 0, "P3", "S", "N"])
+
+
+# every form of the short-block kernel is reached by the shapes its results are checked on
+def test_short_block_cases_reach_every_form(calls):
+    todo, want = [], []
+    for (p, q, k, batch), (tiles, sliced) in CASES:
+        for storage, suffix in enumerate(("", "_f16", "_bf16")[:3 if k >= 8 else 1]):
+            kernels = [f"fc_lane_kernel<{k}, {tiles}, {storage}>"] + ([f"lane_finish_kernel<{k}, {storage}>"] if sliced else [])
+            todo += [fc_forward(p, q, k, batch, suffix), fc_backward(q, p, k, batch, dw=False, suffix=suffix)]
+            want += [kernels] * 2
+    for call, kernels, (st, found) in zip(todo, want, calls(todo)):
+        assert st == 0 and found == kernels, (call, found)
+    forms = {(k, tiles, sliced) for (_, _, k, _), (tiles, sliced) in CASES}
+    assert forms == {(k, t, s) for k in (4, 8, 16, 32) for t, s in ((1, False), (2, False), (1, True))} - {(32, 2, False)}

@@ -12,6 +12,7 @@ from oracle import circ_oracle as O
 from paper_1708_08917_amd import binding as B
 from paper_1708_08917_amd import synth
 from tests import gpu_helpers as G
+from tests.short_block_cases import CASES as SHORT_BLOCK_CASES
 
 pytestmark = pytest.mark.gpu
 
@@ -471,7 +472,8 @@ def test_fc_forward_half_shapes(p, q, k, batch, dtype):
 # ---- short blocks, the one-launch kernel of 16x16 tiles: edges of its tiles (16 block rows, 16 batch rows),
 # of its steps (4 input blocks, 4 waves x 8 of them), slices of the reduction in a second launch (few tiles,
 # long rows) and the form with two tiles of block rows per workgroup (at least 512 of those).  Sums of
-# at most 2000 fp32 terms: the gates of the other tests hold unchanged.
+# at most 2000 fp32 terms: the gates of the other tests hold unchanged.  The route is chosen by estimated times, so some of these
+# take the other routes, which have the same edges; test_fc_short_block_forms has shapes for every form of the kernel.
 @pytest.mark.parametrize("p,q,k,batch", [
     (1, 1, 4, 3), (15, 3, 4, 16), (17, 130, 4, 17), (65, 33, 4, 2731), (4, 700, 4, 18),
     (16, 4, 8, 15), (33, 31, 8, 33), (1, 33, 8, 3), (66, 33, 8, 2731), (5, 520, 8, 19),
@@ -1195,3 +1197,30 @@ def test_conv_backward_data_stride_above_filter(N, p, q, k, H, W, r, pad, stride
     dx, _ = B.circ_conv_backward(B.circ_precompute_spectra(G.dev(w)), None, G.dev(dy), q * k, H, W, r, stride, pad, k, need_dw=False,
                                  workspace=ws)
     check(dx.cpu().numpy(), O.conv_backward_dx(w, dy, H, W, pad, stride), f"dx N={N} {p}x{q} k={k} {H}x{W} r={r} pad={pad} stride={stride}")
+
+
+# ---- every form of the short-block kernel (block size, storage, one and two tiles, sliced reduction), with tails; the
+# gates of the other tests hold for sums of up to 26,000 fp32 terms in chains of at most 1,800.  Sliced reductions also from the
+# library's fixed scratch array.
+@pytest.mark.parametrize("shape,form", SHORT_BLOCK_CASES)
+def test_fc_short_block_forms(shape, form):
+    p, q, k, batch = shape
+    rng = np.random.default_rng(p + q + k + batch)
+    w = (rng.standard_normal((p, q, k)) / np.sqrt(q * k)).astype(np.float32)
+    x = rng.uniform(-1, 1, (batch, q * k)).astype(np.float32)
+    b = (0.1 * rng.standard_normal(p * k)).astype(np.float32)
+    wt = (rng.standard_normal((q, p, k)) / np.sqrt(q * k)).astype(np.float32)      # backward-data of the q x p layer: p outputs
+    what = f"short-block form {p}x{q} k={k} B={batch}"
+    y = G.gpu_fc_forward(w, x, b, relu=True)
+    check(y, O.fc_forward(w, x, b, True), "fwd " + what)
+    check(G.gpu_fc_backward(wt, None, x, need_dw=False)[0], O.fc_backward_dx(wt, x), "dx " + what)
+    if form[1]:
+        y_st = torch.full((batch, p * k), float("nan"), device=G.DEV)
+        B.circ_fc_forward_static(B.circ_precompute_spectra(G.dev(w)), G.dev(x), G.dev(b), y_st, p, q, k, B.EPI_BIAS | B.EPI_RELU)
+        assert np.array_equal(y_st.cpu().numpy(), y), what                         # same kernels, same order
+    if k >= 8:
+        for dtype in HALF_DTYPES:
+            xt, xr = to_half(x, dtype)
+            check_half(gpu_fc_forward_half(w, xt, b, True), O.fc_forward(w, xr, b, True), "fwd " + what, dtype)
+            dxh, _ = B.circ_fc_backward_f16(B.circ_precompute_spectra_f16(G.dev(wt), dtype=dtype), None, xt, q, p, k, need_dw=False)
+            check_half(dxh.float().cpu().numpy(), O.fc_backward_dx(wt, xr), "dx " + what, dtype)

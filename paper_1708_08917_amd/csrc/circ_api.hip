@@ -1195,7 +1195,10 @@ hipError_t launch_conv_fused_q(const float2* wc, const float* x, const float* bi
 namespace {
 
 // The fused CONV kernel serves k = 64, 3x3 filters, 1, 2, 3, 4, 6 or 8 input channel blocks and up
-// to 16 output channel blocks; it keeps offsets inside an image pair in 32 bits.  p, q: output / input channel blocks; H x W the
+// to 16 output channel blocks; it keeps offsets inside an image pair in 32 bits.  The choice goes by shape alone: right for
+// large images (28x28, 4 x 4 blocks, batch 32: 43.7 us, three kernels 49.7; 56x56, 2 x 2 blocks, batch 8: 27.6 against 34.6), while
+// on odd and small ones the three kernels have become the faster (13x13, 6 x 6 blocks, batch 32: 39.3 against 31.2; 7x7, 4 x 4
+// blocks: 36.4 against 13.9; 14x14: 29.7 against 23.7).  p, q: output / input channel blocks; H x W the
 // input image, Ho x Wo the output image.
 inline bool conv_fused_applicable(int p, int q, int k, int r, int N, int H, int W, int Ho, int Wo) {
   const long long HW = (long long)H * W, HWo = (long long)Ho * Wo;
@@ -1407,7 +1410,7 @@ static long long conv_dw_pix_per_block(long long npix) {
 }
 
 // Weight-gradient reduction of a CONV layer: the kernel with the input spectra staged in LDS when
-// a band of rows of 4 input blocks fits 48 KB, else the one that reads every tap from global memory.
+// a band of rows of 4 input and 4 output blocks fits 40 KB, else the one that reads every tap from global memory.
 struct ConvDwPlan {
   bool lds;
   int ng, BR, nbands, cpb, nparts;
@@ -1552,7 +1555,8 @@ circ_status conv_backward_impl(const void* w_hat, const float* x, const float* d
       return (unsigned)(((1ll << 32) + d - 1) / d);
     };
     const unsigned mul_hwo = fast_mul(npix, HWo), mul_wo = fast_mul(HWo, Wo);
-    // staged element index / W: indices stay below 48 KB / 32 B, so the multiply-high is exact
+    // staged element index / W: at most 64 KB of LDS (conv_dw9_kernel) hold indices below 2048 of four planes, and W is no larger,
+    // so the multiply-high is exact
     const unsigned mul_w = (unsigned)(((1ll << 32) + W - 1) / W);
     if (dpl.lds) {
       const unsigned mul_wo_b = (unsigned)(((1ll << 32) + Wo - 1) / Wo);   // pixel index inside a band / Wo

@@ -8,7 +8,8 @@
 // (zero outside the image; written for stride 1 - with stride s the output pixel (ho, wo) pairs
 // with the input pixel (ho*s+dh-pad, wo*s+dw-pad)).  The first is the forward contraction with the
 // conjugated, transposed operand, the offsets reflected and the padding r-1-pad (for s > 1 on the
-// output gradient with s-1 zeros between its pixels), so it runs on conv_contract_kernel; the
+// output gradient with s-1 zeros between its pixels), so it runs on
+// the forward kernels (conv_fused_kernel, or conv_contract_lds_kernel / conv_contract_kernel; circ_api.hip chooses); the
 // second is a reduction over all output pixels (kernels below).
 // The bias gradient of Eq. 1 (a = Wx + theta) is dL/da summed over everything but the channel.
 #pragma once

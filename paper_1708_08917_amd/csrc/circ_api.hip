@@ -628,7 +628,9 @@ inline LanePlan plan_lane(int p, int q, int k, int batch, size_t part_bytes) {
 // 4096 -> 1000 k = 8 batch 256 27.7 -> 12.7 us, 512 x 2048 blocks of 8, batch 32: 66.5 -> 19.1 us, 4096 -> 4096
 // k = 16 batch 256 31.5 -> 20.2 us, 2112 -> 1280 k = 32 batch 700 30.0 -> 18.2 us (16-bit 33.3 -> 18.3 us); kept on the
 // other route: 4096 -> 4096 k = 32 batch 64 8.7 us against 24.5 us, k = 16 batch 1024 with 16-bit storage 35.6
-// against 53.4 us.  Over 200 shapes of 3 to 1024 batch rows the choice costs at most 9 % against the better one.
+// against 53.4 us.  Of 850 random calls of 3 to 1500 batch rows none was more than 5 % slower than on the other routes; the
+// estimates err on their side, most with 16-bit storage and long rows (867 x 1778 blocks of 16, batch 30: 321 us where this
+// kernel takes 84).
 // Times of the other routes, fitted to measurements (us):
 // fused kernel (32): every workgroup of two batch rows costs about the same per chunk of 64 input blocks;
 // three kernels: launches, the serial reduction of the contraction, its arithmetic, the passes over x and y.

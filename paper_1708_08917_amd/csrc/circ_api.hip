@@ -16,6 +16,7 @@
 #include "circ_gemv.h"
 #include "circ_lane.h"
 #include "circ_conv_fused.h"
+#include "circ_conv_lds.h"
 #include "circ_conv_bwd.h"
 #include "circ_update.h"
 #include "circ_half.h"
@@ -1237,24 +1238,99 @@ namespace {
 // tap's index arithmetic then serve twice the products, and 5..7 output blocks no longer cost a
 // second, mostly empty pass over the input (6 x 6 blocks of 64, 26 x 26 stride 2, batch 32:
 // 66 -> 37 us).
+inline unsigned mul_of(long long d) { return (unsigned)(((1ll << 32) + d - 1) / d); }
+
+// Chunks of the staged contraction (contract_chunks): PX groups of 64 pixels per wave, NJ input blocks per step; PX = 0: does
+// not apply.  3x3 and 5x5 filters (the unrolled offsets; with a loop over them 5x5 took 15 to 25 % longer and no less than
+// the bands); up to 4 staged elements per thread, 8 for 3x3 filters with enough steps to hide that they are requested so
+// much later (strides: 30 x 1 block of 512, 32x32 stride 2 85 -> 73 us, but 18 x 20 blocks of 16, 11x11 24.5 -> 28 us with
+// 54 steps).  The form is the one of least estimated time.  Over 600 random shapes the layer takes 0.91 of its
+// time with bands on average (down to 0.25 with many input blocks, whose bands are short) and one is slower by more than
+// 5 % (5 x 1 blocks of 32, 127x127, one image: 26.2 -> 30.0 us).  Blocks of 2 and 3 points keep their routes, which tests hold.
+struct ConvChunkPlan { int PX, U, NJ; unsigned wgs; size_t lds; long long rows, items; };
+inline ConvChunkPlan plan_conv_chunks(int it, int pout, int qin, int NF, int N, int H, int W, int Ho, int Wo, int r, int pad, int stride) {
+  ConvChunkPlan best{};
+  const long long Hp = (long long)H + 2 * pad, Wp = (long long)W + 2 * pad, taps = (long long)r * r;
+  const long long npix = (long long)N * Ho * Wo, plane = (long long)N * H * W;
+  // multiply-high divisions by W, Wo, Hp and Ho; byte offsets inside a plane and weight offsets in 32 bits
+  if ((r != 3 && r != 5) || NF < 3 || W < 2 || Wo < 2 || Wp > 4096 || Hp > 32768 || plane > (1ll << 28) || npix > (1ll << 28) ||
+      taps * NF * qin * pout >= (1ll << 31))
+    return best;
+  long long best_cost = 0;
+  for (int px = 2; px >= 1; --px) {
+    const long long cp = 256 * px, m = (cp - 2) / Wo + 2, cross = (m - 2) / Ho + 1, jump = Hp - (long long)Ho * stride;
+    long long rows = (m - 1) * stride + r + cross * (jump > 0 ? jump : 0);   // padded input rows under a chunk, at most
+    if (rows > N * Hp) rows = N * Hp;
+    const long long ne = rows * W, items = cdiv(npix, cp) * NF * cdiv(pout, it);
+    const int u = ne <= 1024 ? 4 : 8;
+    if (ne > 2048 || (u == 8 && (px == 2 || r != 3 || items * cdiv(qin, 2) < 1024))) continue;
+    for (int nj = u == 8 ? 2 : 5; nj >= 1; --nj) {
+      if (nj > qin) continue;
+      const long long njg = cdiv(qin, nj), wf = cdiv(cdiv(taps, 16 / nj) * 16 * it * 8, 16), lds = 32 * ((nj + 1) / 2 * rows * Wp + wf);
+      if (lds > 80 * 1024) continue;
+      // cycles of a wave in a step: products, staging, a fixed part; 2,500 of latency that the other workgroups of the CU hide
+      const long long own = px * nj * taps * it * 8 + cdiv(ne, 256) * nj * 40 + 600;
+      for (long long res = 160 * 1024 / lds > 3 ? 3 : 160 * 1024 / lds; res >= 1; --res) {
+        const long long wgs = items < 256 * res ? items : 256 * res, per = cdiv(items, wgs), on = cdiv(wgs, 256);
+        const long long cost = per * njg * (own + 2500 > on * own ? own + 2500 : on * own);
+        if (best.PX == 0 || cost < best_cost) {
+          best_cost = cost;
+          best = ConvChunkPlan{px, u, nj, (unsigned)wgs, size_t(lds), rows, items};
+        }
+      }
+    }
+  }
+  return best;
+}
+template <int IT, int PX, int U, int NJ, int R>
+hipError_t launch_conv_lds_t(dim3 grid, size_t lds, const float2* what, const float2* xh, float2* yh, const ConvLdsArgs& a, hipStream_t s) {
+  static LdsOptIn opted;   // the size depends on the image: granted sizes only grow
+  if (ensure_lds(&conv_contract_lds_kernel<IT, PX, U, NJ, R>, lds, opted) != hipSuccess) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((conv_contract_lds_kernel<IT, PX, U, NJ, R>), grid, dim3(256), lds, s, what, xh, yh, a);
+  return hipGetLastError();
+}
+template <int IT>
+hipError_t launch_conv_chunks(const ConvChunkPlan& pl, const float2* what, const float2* xh, float2* yh, int pout, int qin, int NF, int N,
+                              int H, int W, int Ho, int Wo, int r, int pad, int flip, int stride, hipStream_t s) {
+  ConvLdsArgs a{pout, qin, NF, N, H, W, Ho, Wo, r, pad, flip, stride};
+  a.ps = int(pl.rows * (W + 2 * pad));
+  a.ne = int(pl.rows * W);
+  a.wf = int(cdiv(cdiv(r * r, 16 / pl.NJ) * 16 * IT * 8, 16));
+  a.nitems = unsigned(pl.items);
+  a.npix = unsigned(N) * unsigned(Ho) * unsigned(Wo);
+  a.mul_w = mul_of(W);
+  a.mul_hp = mul_of(H + 2 * pad);
+  a.mul_wo = mul_of(Wo);
+  a.mul_ho = Ho > 1 ? mul_of(Ho) : 0u;
+#define CIRC_CHUNKS(px, u, nj, rr) \
+  if (pl.PX == px && pl.U == u && pl.NJ == nj && r == rr) return launch_conv_lds_t<IT, px, u, nj, rr>(dim3(pl.wgs), pl.lds, what, xh, yh, a, s);
+#define CIRC_CHUNKS_NJ(px, rr) \
+  CIRC_CHUNKS(px, 4, 1, rr) CIRC_CHUNKS(px, 4, 2, rr) CIRC_CHUNKS(px, 4, 3, rr) CIRC_CHUNKS(px, 4, 4, rr) CIRC_CHUNKS(px, 4, 5, rr)
+  CIRC_CHUNKS_NJ(1, 3) CIRC_CHUNKS_NJ(2, 3) CIRC_CHUNKS_NJ(1, 5) CIRC_CHUNKS_NJ(2, 5)
+  CIRC_CHUNKS(1, 8, 1, 3) CIRC_CHUNKS(1, 8, 2, 3)
+#undef CIRC_CHUNKS_NJ
+#undef CIRC_CHUNKS
+  return hipErrorInvalidValue;
+}
+
 // G images x BR output rows per workgroup of the staged contraction; G = 0: does not apply.  Among the
 // chunks whose spectra and weights fit 48 KB (of at most 64 bands per image), the one with the least work per CU: rounds
 // of 64 pixels on four waves, staged values, a fixed part of about 1 us (cycles below), four workgroups of a CU
 // side by side (three above 40 KB, for which the estimate is low).
-struct ConvLdsPlan { int G, BR, nbands, pstride; size_t lds; };
+struct ConvBandPlan { int G, BR, nbands, pstride; size_t lds; };
 // Whether the best chunk is worth staging: it is if its staged values, weights included, are few against the products that
 // read them (2.4 and more each), and otherwise (strides of the filter size and more, chunks of a few pixels) only
 // where all workgroups are resident at once, where what counts is that the loads go out together.  Over 725 shapes
 // (2x2 to 7x7, strides 1 to 5) staging always costs 2.8 % on average against the better form and up to 7 times (81 x 34
 // blocks of 8, 112x10 stride 4: 460 us against 66), never 21 %; this rule 0.7 % and at most 1.35 times.
-inline bool conv_lds_pays(const ConvLdsPlan& pl, int it, int pout, int NF, int N, int W, int Wo, int r, int pad, int stride) {
+inline bool conv_bands_pay(const ConvBandPlan& pl, int it, int pout, int NF, int N, int W, int Wo, int r, int pad, int stride) {
   const long long plane = ((long long)(pl.BR - 1) * stride + r) * (W + 2 * pad), taps = (long long)r * r;
   const long long staged = pl.G * plane + taps * it, reads = (long long)pl.G * pl.BR * Wo * taps;   // per input block
   const long long wgs = cdiv(N, pl.G) * pl.nbands * NF * cdiv(pout, it), room = 160 * 1024 / (long long)pl.lds;
   return 12 * staged <= 5 * reads || wgs <= 256 * (room < 8 ? room : 8);
 }
-inline ConvLdsPlan plan_conv_lds(int it, int pout, int qin, int NF, int N, int W, int Ho, int Wo, int r, int pad, int stride) {
-  ConvLdsPlan best{0, 0, 0, 0, 0};
+inline ConvBandPlan plan_conv_bands(int it, int pout, int qin, int NF, int N, int W, int Ho, int Wo, int r, int pad, int stride) {
+  ConvBandPlan best{0, 0, 0, 0, 0};
   const long long Wp = (long long)W + 2 * pad, taps = (long long)r * r, wbytes = taps * qin * it * 8;
   if (Wp < 2 || Wo < 2 || Wp > 4096 || qin > 64) return best;
   double best_cost = 0;
@@ -1267,7 +1343,7 @@ inline ConvLdsPlan plan_conv_lds(int it, int pout, int qin, int NF, int N, int W
     const double cost = wg * (wgs > 1024 ? wgs / 1024.0 : 1.0);
     if (best.G == 0 || cost < best_cost) {
       best_cost = cost;
-      best = ConvLdsPlan{G, BR, (int)nb, (int)ps, (size_t)lds};
+      best = ConvBandPlan{G, BR, (int)nb, (int)ps, (size_t)lds};
     }
   };
   for (int nb = 1; nb <= Ho && nb <= 64; ++nb) consider(1, (int)cdiv(Ho, nb));
@@ -1275,15 +1351,20 @@ inline ConvLdsPlan plan_conv_lds(int it, int pout, int qin, int NF, int N, int W
   return best;
 }
 template <int IT>
-hipError_t launch_conv_contract_lds(const ConvLdsPlan& pl, const float2* what, const float2* xh, float2* yh, int pout, int qin,
-                                    int NF, int N, int H, int W, int Ho, int Wo, int r, int pad, int flip, int stride,
-                                    hipStream_t s) {
-  auto mul = [](long long d) { return (unsigned)(((1ll << 32) + d - 1) / d); };
+hipError_t launch_conv_bands(const ConvBandPlan& pl, const float2* what, const float2* xh, float2* yh, int pout, int qin, int NF, int N,
+                             int H, int W, int Ho, int Wo, int r, int pad, int flip, int stride, hipStream_t s) {
+  ConvLdsArgs a{pout, qin, NF, N, H, W, Ho, Wo, r, pad, flip, stride};
   const long long Wp = W + 2 * pad, plane = ((long long)(pl.BR - 1) * stride + r) * Wp;
+  a.ps = pl.pstride;
+  a.G = pl.G;
+  a.BR = pl.BR;
+  a.nbands = pl.nbands;
+  a.mul_pl = mul_of(plane);
+  a.mul_wp = mul_of(Wp);
+  a.mul_px = mul_of((long long)pl.BR * Wo);
+  a.mul_wo = mul_of(Wo);
   const dim3 grid((unsigned)(cdiv(N, pl.G) * pl.nbands), (unsigned)NF, (unsigned)cdiv(pout, IT));
-  hipLaunchKernelGGL((conv_contract_lds_kernel<IT>), grid, dim3(256), pl.lds, s, what, xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r, pad,
-                     flip, stride, pl.G, pl.BR, pl.nbands, pl.pstride, mul(plane), mul(Wp), mul((long long)pl.BR * Wo), mul(Wo));
-  return hipGetLastError();
+  return launch_conv_lds_t<IT, 0, 0, 0, 0>(grid, pl.lds, what, xh, yh, a, s);
 }
 template <int IT, int JQ>
 hipError_t launch_conv_contract_j(const float2* what, const float2* xh, float2* yh, int pout, int qin, int NF, int N, int H,
@@ -1313,10 +1394,14 @@ hipError_t launch_conv_contract(const float2* what, const float2* xh, float2* yh
   // 5x5, 20x20, batch 16: 65 -> 32 us)
   if (dil == 1 && r > 1) {
     const int it = pout > 4 ? 8 : 4;
-    const ConvLdsPlan pl = plan_conv_lds(it, pout, qin, NF, N, W, Ho, Wo, r, pad, stride);
-    if (pl.G > 0 && conv_lds_pays(pl, it, pout, NF, N, W, Wo, r, pad, stride))
-      return it == 8 ? launch_conv_contract_lds<8>(pl, what, xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r, pad, flip, stride, s)
-                     : launch_conv_contract_lds<4>(pl, what, xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r, pad, flip, stride, s);
+    const ConvChunkPlan cl = plan_conv_chunks(it, pout, qin, NF, N, H, W, Ho, Wo, r, pad, stride);
+    if (cl.PX > 0)
+      return it == 8 ? launch_conv_chunks<8>(cl, what, xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r, pad, flip, stride, s)
+                     : launch_conv_chunks<4>(cl, what, xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r, pad, flip, stride, s);
+    const ConvBandPlan pl = plan_conv_bands(it, pout, qin, NF, N, W, Ho, Wo, r, pad, stride);
+    if (pl.G > 0 && conv_bands_pay(pl, it, pout, NF, N, W, Wo, r, pad, stride))
+      return it == 8 ? launch_conv_bands<8>(pl, what, xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r, pad, flip, stride, s)
+                     : launch_conv_bands<4>(pl, what, xh, yh, pout, qin, NF, N, H, W, Ho, Wo, r, pad, flip, stride, s);
   }
   // input blocks per request: the group size of 3 or 4 that leaves fewer empty places, or all of them
 #define CIRC_CONTRACT_J(IT)                                                                                                      \

@@ -1,0 +1,370 @@
+// Contraction of a CONV layer over filter offsets and input blocks with the spectra staged in LDS
+// (undilated input):  Y^[f][i][pixel] = sum_{t, j} W^[t][f][j][i] X^[f][j][pixel under offset t].
+//
+// Two forms.  contract_chunks (3x3 and 5x5 filters) is a pipeline: a workgroup walks over items (chunk of 256 PX output
+// pixels, frequency, group of IT output blocks) and inside an item over groups of NJ input blocks; the spectra of the next
+// step are requested before the products of the present one and wait in registers for the other of two LDS buffers.
+// contract_bands stages all input blocks of a band of rows at once and then multiplies: everything the first form does not
+// take (other filter sizes, strides and images whose rows under a chunk exceed its registers).
+// Where the time went in the bands form (25,088 pixels, 4 x 4 blocks of 64, 3x3: 27.2 us where the products need 7 and
+// the 60 MB of spectra 11): LDS reads, two per four products, took as long as the products, and all workgroups of
+// the chip staged, multiplied and stored in step.  In chunks: one LDS read of 16 bytes per eight products (two input
+// blocks side by side; the weights of 16 / NJ offsets sit in one register pair, whose 16 blocks of 4 the matrix
+// instruction hands out, CBSZ = 4), buffer descriptors (a 32-bit offset per lane, nothing to mask: what is outside the
+// image reads as zero), unrolled offsets: 20 us.  4 x 4 blocks of 96, 13x13, batch 32: 13.1 -> 10.5 us; 4 x 4 of 64, 28x28,
+// 5x5: 83.6 -> 60.8 us for the layer.  Left: products, staging and the launch do not overlap fully (6.3 items per CU).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+#include <utility>
+
+#include "circ_kernels.h"
+
+namespace circ {
+
+constexpr int kConvBufferFlags = 0x00027000;   // raw buffer descriptor, 32-bit data
+constexpr unsigned kConvNowhere = 0x80000000u; // byte offset past every plane: loads give 0, stores are dropped
+typedef unsigned conv_uintx2 __attribute__((ext_vector_type(2)));
+
+struct ConvLdsArgs {
+  int p, q, NF, Nimg, H, W, Ho, Wo, r, pad, flip, stride;
+  int ps;                                     // LDS pitch of the planes
+  unsigned mul_wo;                            // mul_d: ceil(2^32 / d), exact division of the small indices below by a multiply-high
+  int ne, wf;                                 // chunks: staged elements per input block, float4 of weights
+  unsigned nitems, npix, mul_w, mul_hp, mul_ho;   // (mul_ho = 0 for Ho = 1)
+  int G, BR, nbands;                          // bands: images and output rows per workgroup
+  unsigned mul_pl, mul_wp, mul_px;
+};
+
+// f(integral_constant 0), ..., f(integral_constant N - 1)
+template <class F, int... I>
+__device__ __forceinline__ void unrolled_seq(const F& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void unrolled(const F& f) { unrolled_seq(f, std::make_integer_sequence<int, N>{}); }
+
+// acc += w x with w from block ABID of the instruction's 16 blocks, for all of them
+template <int ABID>
+__device__ __forceinline__ floatx4 mfma_bcast(float w, float x, floatx4 acc) {
+  return __builtin_amdgcn_mfma_f32_4x4x1f32(w, x, acc, 4, ABID, 0);
+}
+
+// Bands of rows: a workgroup takes, for one
+// frequency and one group of IT output blocks, the output rows [ho0, ho0 + BR) of G images: it stages
+// the input rows under them of all q blocks, zero columns and rows around the image included, and the
+// frequency's weights in one burst of loads, and everything after the barrier runs from LDS: per (tap,
+// input block) and 64 pixels two LDS reads and four 4x4x1 matrix instructions per 4 output blocks.  The kernel
+// above waits for memory at every tap, and its nine reads of a value pass through the cache one by one.
+// LDS: q planes of `pstride` values, then r*r*q*IT weights.  mul_*: ceil(2^32 / d) for the divisions by
+// rows_in*(W+2*pad), W+2*pad, BR*Wo and Wo (indices and divisors below 2^16: exact).
+template <int IT>
+__device__ __forceinline__ void contract_bands(const float2* __restrict__ What, const float2* __restrict__ Xh, float2* __restrict__ Yh,
+                                               const ConvLdsArgs& a) {
+  extern __shared__ __attribute__((aligned(16))) float4 cps[];
+  float2* cxs = reinterpret_cast<float2*>(cps);
+  const int p = a.p, q = a.q, NF = a.NF, Nimg = a.Nimg, H = a.H, W = a.W, Ho = a.Ho, Wo = a.Wo, r = a.r, pad = a.pad, flip = a.flip;
+  const int stride = a.stride, G = a.G, BR = a.BR, nbands = a.nbands, pstride = a.ps;
+  const unsigned mul_pl = a.mul_pl, mul_wp = a.mul_wp, mul_px = a.mul_px, mul_wo = a.mul_wo;
+  constexpr int IG = IT / 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), f = blockIdx.y;
+  const int i0 = blockIdx.z * IT, chunk = blockIdx.x, n0 = chunk / nbands * G, ho0 = (chunk % nbands) * BR;
+  const int Wp = W + 2 * pad, rows_in = (BR - 1) * stride + r, pl = rows_in * Wp, taps = r * r;
+  const unsigned HW = unsigned(H) * unsigned(W);
+  float2* ws = cxs + q * pstride;
+
+  // weights [tap][j][i], the reflected filter's tap order with flip; blocks past p repeat the last one
+  for (int e = tid; e < taps * q * IT; e += 256) {
+    const int i = e % IT, tj = e / IT, t = tj / q, j = tj - t * q;
+    ws[e] = What[((long long)(flip ? taps - 1 - t : t) * NF + f) * q * p + (long long)j * p + min(i0 + i, p - 1)];
+  }
+  const int hfirst = ho0 * stride - pad;
+  for (int e = tid; e < G * pl; e += 256) {
+    const int g = int(__umulhi(unsigned(e), mul_pl)), rem = e - g * pl, row = int(__umulhi(unsigned(rem), mul_wp));
+    const int hi = hfirst + row, wi = rem - row * Wp - pad, n = n0 + g;
+    const bool in = unsigned(hi) < unsigned(H) && unsigned(wi) < unsigned(W) && n < Nimg;
+    const unsigned o = in ? unsigned(n) * HW + unsigned(hi * W + wi) : 0u;
+    const float2* src = Xh + (long long)f * q * Nimg * HW;
+    int j = 0;
+    for (; j + 4 <= q; j += 4) {
+      float2 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = (src + (long long)(j + u) * Nimg * HW)[o];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) cxs[(j + u) * pstride + e] = in ? v[u] : make_float2(0.f, 0.f);
+    }
+    for (; j < q; ++j) {
+      const float2 v = (src + (long long)j * Nimg * HW)[o];
+      cxs[j * pstride + e] = in ? v : make_float2(0.f, 0.f);
+    }
+  }
+  __syncthreads();
+
+  const int npx = BR * Wo, total = G * npx;
+  const float2* wl = ws + (lane & 3);
+  for (int g0 = wave * 64; g0 < total; g0 += 256) {
+    const int px = min(g0 + lane, total - 1);                   // lanes past the end take part with the last pixel
+    const int g = int(__umulhi(unsigned(px), mul_px)), rem = px - g * npx, hl = int(__umulhi(unsigned(rem), mul_wo)), wo = rem - hl * Wo;
+    const float2* xl = cxs + g * pl + (hl * Wp + wo) * stride;
+    ContractSums<IG> acc;
+    acc.clear();
+    const float2* wt = wl;
+    for (int dh = 0; dh < r; ++dh) {
+      for (int dw = 0; dw < r; ++dw) {
+        const float2* xt = xl + dh * Wp + dw;
+        auto block = [&](auto NJ) {                             // NJ input blocks: operands first, then the products
+          constexpr int N = decltype(NJ)::value;
+          float2 x[N], w[N][IG];
+#pragma unroll
+          for (int u = 0; u < N; ++u) {
+            x[u] = xt[u * pstride];
+#pragma unroll
+            for (int h = 0; h < IG; ++h) w[u][h] = wt[u * IT + 4 * h];
+          }
+#pragma unroll
+          for (int u = 0; u < N; ++u) acc.add(w[u], x[u]);
+          xt += N * pstride;
+          wt += N * IT;
+        };
+        int j = 0;
+        for (; j + 4 <= q; j += 4) block(std::integral_constant<int, 4>{});
+        for (; j + 2 <= q; j += 2) block(std::integral_constant<int, 2>{});
+        if (j < q) block(std::integral_constant<int, 1>{});
+      }
+    }
+    const int n = n0 + g, ho = ho0 + hl;
+    if (g0 + lane < total && n < Nimg && ho < Ho) {
+#pragma unroll
+      for (int ii = 0; ii < IT; ++ii)
+        if (i0 + ii < p)
+          Yh[(((long long)f * p + i0 + ii) * Nimg + n) * Ho * Wo + ho * Wo + wo] = acc.sum(ii);
+    }
+  }
+}
+
+// Chunks of 256 PX consecutive output pixels of all images (px = (n*Ho + ho)*Wo + wo, the order of Yh): lane = pixel, IT
+// output blocks and PX groups of 64 pixels per wave, U staged elements per thread and input block, NJ input blocks per step.
+// The rows under a chunk are staged with their zero columns, those between two images with the zero rows of either.
+// Products with either part of the weights are summed apart (as in ContractSums), in the order of offsets and input blocks.
+// Workgroup b takes the items [b nitems / grid, (b + 1) nitems / grid).
+// LDS: two buffers of (NJ + 1) / 2 planes of `ps` float4 (two input blocks side by side) and wf float4 of weights [t][j][i].
+template <int IT, int PX, int U, int NJ, int R>
+__device__ __forceinline__ void contract_chunks(const float2* __restrict__ What, const float2* __restrict__ Xh, float2* __restrict__ Yh,
+                                                const ConvLdsArgs& a) {
+  extern __shared__ __attribute__((aligned(16))) float4 cps[];
+  constexpr int IG = IT / 4, CP = 256 * PX, UW = 2, taps = R * R, NPL = (NJ + 1) / 2, TG = 16 / NJ;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), blk = lane >> 2, sub = lane & 3;
+  const int Wp = a.W + 2 * a.pad, Hp = a.H + 2 * a.pad, nw = taps * NJ * IT;
+  const int nig = (a.p + IT - 1) / IT, njg = (a.q + NJ - 1) / NJ, bsz = NPL * a.ps + a.wf;
+  const unsigned item0 = unsigned((unsigned long long)blockIdx.x * a.nitems / gridDim.x);
+  const unsigned item1 = unsigned((unsigned long long)(blockIdx.x + 1) * a.nitems / gridDim.x);
+  const int nsteps = int(item1 - item0) * njg;
+  const long long plane = (long long)a.Nimg * a.H * a.W;
+
+  int rig, rf, rjg = 0;                      // the next step to request
+  unsigned rc;
+  {
+    unsigned t = item0 / unsigned(nig);
+    rig = int(item0 - t * unsigned(nig));
+    rc = t / unsigned(a.NF);
+    rf = int(t - rc * unsigned(a.NF));
+  }
+  int cig = rig, cf = rf, cjg = 0;           // the step being computed
+  unsigned cc = rc;
+  auto chunk_origin = [&](unsigned c, int& n0, int& ho0) {
+    const unsigned r0 = c * CP / unsigned(a.Wo);
+    n0 = int(r0 / unsigned(a.Ho));
+    ho0 = int(r0) - n0 * a.Ho;
+  };
+  // staged elements of this thread: byte offset in an input plane, place in LDS
+  unsigned xoff[U];
+  int dst[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const unsigned e = tid + 256 * u;
+    dst[u] = int(e) + int(__umulhi(e, a.mul_w)) * 2 * a.pad + a.pad;      // row * Wp + pad + column
+  }
+  auto locate = [&](unsigned c) {
+    int n0, ho0;
+    chunk_origin(c, n0, ho0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const unsigned e = tid + 256 * u;
+      const int row = int(__umulhi(e, a.mul_w)), col = int(e) - row * a.W;
+      const int lp = ho0 * a.stride + row, dn = int(__umulhi(unsigned(lp), a.mul_hp)), h = lp - dn * Hp - a.pad, n = n0 + dn;
+      const bool ok = unsigned(h) < unsigned(a.H) && n < a.Nimg;
+      xoff[u] = ok ? (unsigned(n * a.H + h) * unsigned(a.W) + unsigned(col)) * 8u : kConvNowhere;
+    }
+  };
+  // this thread's weights: [tap][j][i] in LDS
+  unsigned woff[UW];
+#pragma unroll
+  for (int u = 0; u < UW; ++u) {
+    const int e = tid + 256 * u, i = e % IT, pj = e / IT, t = pj / NJ, j = pj - t * NJ;
+    woff[u] = unsigned(((a.flip ? taps - 1 - t : t) * a.NF * a.q + j) * a.p + i);
+  }
+  conv_uintx2 xv[U][NJ];
+  float2 wv[UW];
+  auto weight = [&](int e, unsigned o, int f, int ig, int jg) -> float2 {
+    const int i = e % IT, j = e / IT % NJ;
+    const bool ok = e < nw && NJ * jg + j < a.q && ig * IT + i < a.p;
+    const float2* src = What + ((long long)f * a.q + NJ * jg) * a.p + ig * IT;
+    return ok ? src[o] : make_float2(0.f, 0.f);
+  };
+  auto request = [&]() {
+    const float2* src = Xh + (long long)rf * a.q * plane;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float2*>(src + min(NJ * rjg + j, a.q - 1) * plane), short(0),
+                                                        int(plane * 8), kConvBufferFlags);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (256 * u < a.ne) xv[u][j] = __builtin_amdgcn_raw_buffer_load_b64(rs, int(xoff[u]), 0, 0);   // (uniform)
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UW; ++u) wv[u] = weight(tid + 256 * u, woff[u], rf, rig, rjg);
+  };
+  auto advance = [&](int& ig, int& f, unsigned& c, int& jg) -> bool {   // whether the chunk changes
+    if (++jg < njg) return false;
+    jg = 0;
+    if (++ig < nig) return false;
+    ig = 0;
+    if (++f < a.NF) return false;
+    f = 0;
+    ++c;
+    return true;
+  };
+  auto store = [&](float4* b) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (tid + 256 * u < a.ne) {
+        typedef unsigned u4 __attribute__((ext_vector_type(4)));
+#pragma unroll
+        for (int l = 0; l < NPL; ++l) {
+          const conv_uintx2 v0 = xv[u][2 * l], v1 = 2 * l + 1 < NJ ? xv[u][2 * l + 1 < NJ ? 2 * l + 1 : 0] : conv_uintx2{0u, 0u};
+          *reinterpret_cast<u4*>(b + l * a.ps + dst[u]) = u4{v0.x, v0.y, v1.x, v1.y};
+        }
+      }
+    }
+    float2* w = reinterpret_cast<float2*>(b + NPL * a.ps);
+#pragma unroll
+    for (int u = 0; u < UW; ++u)
+      if (tid + 256 * u < nw) w[tid + 256 * u] = wv[u];
+    for (int e = tid + 256 * UW; e < nw; e += 256) {
+      const int i = e % IT, pj = e / IT, t = pj / NJ, j = pj - t * NJ;
+      w[e] = weight(e, unsigned(((a.flip ? taps - 1 - t : t) * a.NF * a.q + j) * a.p + i), cf, cig, cjg);
+    }
+  };
+
+  locate(rc);
+  if (nsteps > 0) request();
+  for (int e = tid; e < 2 * bsz; e += 256) cps[e] = make_float4(0.f, 0.f, 0.f, 0.f);   // the margins stay zero
+  int lb[PX];
+  unsigned yoff[PX], ooff[PX];
+  auto pixels = [&](unsigned c) {
+    int n0, ho0;
+    chunk_origin(c, n0, ho0);
+    const unsigned first = (unsigned(n0) * unsigned(a.Ho) + unsigned(ho0)) * unsigned(a.Wo);
+#pragma unroll
+    for (int g = 0; g < PX; ++g) {
+      const unsigned px = c * CP + (wave * PX + g) * 64 + lane, lpx = min(px, a.npix - 1) - first;
+      const int rl = int(__umulhi(lpx, a.mul_wo)), wo = int(lpx) - rl * a.Wo;
+      const int ra = ho0 + rl, dn = a.mul_ho ? int(__umulhi(unsigned(ra), a.mul_ho)) : ra, ho = ra - dn * a.Ho;
+      lb[g] = (dn * Hp + (ho - ho0) * a.stride) * Wp + wo * a.stride;
+      yoff[g] = px < a.npix ? px * 8u : kConvNowhere;
+    }
+  };
+  pixels(cc);
+  floatx4 wrxr[PX][IG], wrxi[PX][IG], wixr[PX][IG], wixi[PX][IG];
+  // the sums of a finished item leave behind the barrier of the next step, ahead of its requests: the wait for those does
+  // not include the stores
+  int oig = 0, of = 0;
+  bool odone = false;
+#pragma unroll
+  for (int g = 0; g < PX; ++g) ooff[g] = kConvNowhere;
+  auto output = [&]() {
+    if (!odone) return;
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      if (oig * IT + i < a.p) {
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc(Yh + ((long long)of * a.p + oig * IT + i) * a.npix, short(0), int(a.npix * 8u), kConvBufferFlags);
+#pragma unroll
+        for (int g = 0; g < PX; ++g) {
+          const conv_uintx2 v{__float_as_uint(wrxr[g][i / 4][i % 4] - wixi[g][i / 4][i % 4]), __float_as_uint(wrxi[g][i / 4][i % 4] + wixr[g][i / 4][i % 4])};
+          __builtin_amdgcn_raw_buffer_store_b64(v, rs, int(ooff[g]), 0, 0);
+        }
+      }
+    }
+  };
+  __syncthreads();
+
+  for (int s = 0; s < nsteps; ++s) {
+    float4* b = cps + (s & 1) * bsz;
+    store(b);
+    __syncthreads();
+    output();
+    if (s + 1 < nsteps) {
+      if (advance(rig, rf, rc, rjg)) locate(rc);
+      request();
+    }
+    if (cjg == 0) {
+#pragma unroll
+      for (int g = 0; g < PX; ++g)
+#pragma unroll
+        for (int h = 0; h < IG; ++h) wrxr[g][h] = wrxi[g][h] = wixr[g][h] = wixi[g][h] = floatx4{0.f, 0.f, 0.f, 0.f};
+    }
+    if (cc * CP + wave * PX * 64 < a.npix) {
+      const float2* ws = reinterpret_cast<const float2*>(b + NPL * a.ps) + blk * IT + sub;
+      float2 w[IG];
+      auto tap = [&](auto AB, int off) {               // the tap's weights sit in blocks AB, AB + 1, ... of w
+        constexpr int ab = decltype(AB)::value;
+        float4 x[PX][NPL];
+#pragma unroll
+        for (int g = 0; g < PX; ++g)
+#pragma unroll
+          for (int l = 0; l < NPL; ++l) x[g][l] = b[l * a.ps + lb[g] + off];
+        auto mac = [&](auto J) {
+          constexpr int j = decltype(J)::value;
+#pragma unroll
+          for (int g = 0; g < PX; ++g) {
+            const float xr = j & 1 ? x[g][j / 2].z : x[g][j / 2].x, xi = j & 1 ? x[g][j / 2].w : x[g][j / 2].y;
+#pragma unroll
+            for (int h = 0; h < IG; ++h) {
+              wrxr[g][h] = mfma_bcast<ab + j>(w[h].x, xr, wrxr[g][h]);
+              wrxi[g][h] = mfma_bcast<ab + j>(w[h].x, xi, wrxi[g][h]);
+              wixr[g][h] = mfma_bcast<ab + j>(w[h].y, xr, wixr[g][h]);
+              wixi[g][h] = mfma_bcast<ab + j>(w[h].y, xi, wixi[g][h]);
+            }
+          }
+        };
+        unrolled<NJ>(mac);
+      };
+      unrolled<taps>([&](auto TT) {
+        constexpr int t = decltype(TT)::value;
+        if constexpr (t % TG == 0) {
+#pragma unroll
+          for (int h = 0; h < IG; ++h) w[h] = ws[t * NJ * IT + 4 * h];
+        }
+        tap(std::integral_constant<int, t % TG * NJ>{}, t / R * Wp + t % R);
+      });
+    }
+    oig = cig;
+    of = cf;
+    odone = cjg == njg - 1;
+#pragma unroll
+    for (int g = 0; g < PX; ++g) ooff[g] = yoff[g];
+    if (advance(cig, cf, cc, cjg)) pixels(cc);
+  }
+  output();
+}
+template <int IT, int PX, int U, int NJ, int R>
+__global__ __launch_bounds__(256, PX == 0 ? 1 : IT * PX > 8 ? 2 : 3) void conv_contract_lds_kernel(
+    const float2* __restrict__ What, const float2* __restrict__ Xh, float2* __restrict__ Yh, ConvLdsArgs a) {
+  if constexpr (PX == 0) contract_bands<IT>(What, Xh, Yh, a);
+  else contract_chunks<IT, PX, U, NJ, R>(What, Xh, Yh, a);
+}
+
+}  // namespace circ

@@ -871,95 +871,4 @@ __global__ __launch_bounds__(256) void conv_contract_kernel(const float2* __rest
     if (i0 + ii < p) Yh[(((long long)f * p + i0 + ii) * Nimg + n) * Ho * Wo + at] = acc.sum(ii);
 }
 
-// The same contraction with the spectra staged in LDS (undilated input).  A workgroup takes, for one
-// frequency and one group of IT output blocks, the output rows [ho0, ho0 + BR) of G images: it stages
-// the input rows under them of all q blocks, zero columns and rows around the image included, and the
-// frequency's weights in one burst of loads, and everything after the barrier runs from LDS: per (tap,
-// input block) and 64 pixels two LDS reads and four 4x4x1 matrix instructions per 4 output blocks.  The kernel
-// above waits for memory at every tap, and its nine reads of a value pass through the cache one by one.
-// LDS: q planes of `pstride` values, then r*r*q*IT weights.  mul_*: ceil(2^32 / d) for the divisions by
-// rows_in*(W+2*pad), W+2*pad, BR*Wo and Wo (indices and divisors below 2^16: exact).
-template <int IT>
-__global__ __launch_bounds__(256) void conv_contract_lds_kernel(const float2* __restrict__ What, const float2* __restrict__ Xh,
-                                                                float2* __restrict__ Yh, int p, int q, int NF, int Nimg, int H,
-                                                                int W, int Ho, int Wo, int r, int pad, int flip, int stride, int G,
-                                                                int BR, int nbands, int pstride, unsigned mul_pl, unsigned mul_wp,
-                                                                unsigned mul_px, unsigned mul_wo) {
-  extern __shared__ __attribute__((aligned(16))) float2 cxs[];
-  constexpr int IG = IT / 4;
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), f = blockIdx.y;
-  const int i0 = blockIdx.z * IT, chunk = blockIdx.x, n0 = chunk / nbands * G, ho0 = (chunk % nbands) * BR;
-  const int Wp = W + 2 * pad, rows_in = (BR - 1) * stride + r, pl = rows_in * Wp, taps = r * r;
-  const unsigned HW = unsigned(H) * unsigned(W);
-  float2* ws = cxs + q * pstride;
-
-  // weights [tap][j][i], the reflected filter's tap order with flip; blocks past p repeat the last one
-  for (int e = tid; e < taps * q * IT; e += 256) {
-    const int i = e % IT, tj = e / IT, t = tj / q, j = tj - t * q;
-    ws[e] = What[((long long)(flip ? taps - 1 - t : t) * NF + f) * q * p + (long long)j * p + min(i0 + i, p - 1)];
-  }
-  const int hfirst = ho0 * stride - pad;
-  for (int e = tid; e < G * pl; e += 256) {
-    const int g = int(__umulhi(unsigned(e), mul_pl)), rem = e - g * pl, row = int(__umulhi(unsigned(rem), mul_wp));
-    const int hi = hfirst + row, wi = rem - row * Wp - pad, n = n0 + g;
-    const bool in = unsigned(hi) < unsigned(H) && unsigned(wi) < unsigned(W) && n < Nimg;
-    const unsigned o = in ? unsigned(n) * HW + unsigned(hi * W + wi) : 0u;
-    const float2* src = Xh + (long long)f * q * Nimg * HW;
-    int j = 0;
-    for (; j + 4 <= q; j += 4) {
-      float2 v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = (src + (long long)(j + u) * Nimg * HW)[o];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) cxs[(j + u) * pstride + e] = in ? v[u] : make_float2(0.f, 0.f);
-    }
-    for (; j < q; ++j) {
-      const float2 v = (src + (long long)j * Nimg * HW)[o];
-      cxs[j * pstride + e] = in ? v : make_float2(0.f, 0.f);
-    }
-  }
-  __syncthreads();
-
-  const int npx = BR * Wo, total = G * npx;
-  const float2* wl = ws + (lane & 3);
-  for (int g0 = wave * 64; g0 < total; g0 += 256) {
-    const int px = min(g0 + lane, total - 1);                   // lanes past the end take part with the last pixel
-    const int g = int(__umulhi(unsigned(px), mul_px)), rem = px - g * npx, hl = int(__umulhi(unsigned(rem), mul_wo)), wo = rem - hl * Wo;
-    const float2* xl = cxs + g * pl + (hl * Wp + wo) * stride;
-    ContractSums<IG> acc;
-    acc.clear();
-    const float2* wt = wl;
-    for (int dh = 0; dh < r; ++dh) {
-      for (int dw = 0; dw < r; ++dw) {
-        const float2* xt = xl + dh * Wp + dw;
-        auto block = [&](auto NJ) {                             // NJ input blocks: operands first, then the products
-          constexpr int N = decltype(NJ)::value;
-          float2 x[N], w[N][IG];
-#pragma unroll
-          for (int u = 0; u < N; ++u) {
-            x[u] = xt[u * pstride];
-#pragma unroll
-            for (int h = 0; h < IG; ++h) w[u][h] = wt[u * IT + 4 * h];
-          }
-#pragma unroll
-          for (int u = 0; u < N; ++u) acc.add(w[u], x[u]);
-          xt += N * pstride;
-          wt += N * IT;
-        };
-        int j = 0;
-        for (; j + 4 <= q; j += 4) block(std::integral_constant<int, 4>{});
-        for (; j + 2 <= q; j += 2) block(std::integral_constant<int, 2>{});
-        if (j < q) block(std::integral_constant<int, 1>{});
-      }
-    }
-    const int n = n0 + g, ho = ho0 + hl;
-    if (g0 + lane < total && n < Nimg && ho < Ho) {
-#pragma unroll
-      for (int ii = 0; ii < IT; ++ii)
-        if (i0 + ii < p)
-          Yh[(((long long)f * p + i0 + ii) * Nimg + n) * Ho * Wo + ho * Wo + wo] = acc.sum(ii);
-    }
-  }
-}
-
 }  // namespace circ

@@ -12,6 +12,7 @@ import textwrap
 
 import pytest
 
+from tests.conv_chunk_cases import CASES as CHUNK_CASES
 from tests.short_block_cases import CASES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -160,3 +161,9 @@ def test_short_block_cases_reach_every_form(calls):
         assert st == 0 and found == kernels, (call, found)
     forms = {(k, tiles, sliced) for (_, _, k, _), (tiles, sliced) in CASES}
     assert forms == {(k, t, s) for k in (4, 8, 16, 32) for t, s in ((1, False), (2, False), (1, True))} - {(32, 2, False)}
+
+
+# every form of the contraction in chunks of pixels is reached by the shapes its results are checked on
+def test_conv_chunk_cases_reach_their_forms(calls):
+    for (dims, form), (st, kernels) in zip(CHUNK_CASES, calls([conv_forward(*dims) for dims, _ in CHUNK_CASES])):
+        assert st == 0 and kernels[1] == "conv_contract_lds_kernel<%d, %d, %d, %d, %d>" % form, (dims, kernels)

@@ -12,6 +12,7 @@ from oracle import circ_oracle as O
 from paper_1708_08917_amd import binding as B
 from paper_1708_08917_amd import synth
 from tests import gpu_helpers as G
+from tests.conv_chunk_cases import CASES as CONV_CHUNK_CASES
 from tests.short_block_cases import CASES as SHORT_BLOCK_CASES
 
 pytestmark = pytest.mark.gpu
@@ -1224,3 +1225,17 @@ def test_fc_short_block_forms(shape, form):
             check_half(gpu_fc_forward_half(w, xt, b, True), O.fc_forward(w, xr, b, True), "fwd " + what, dtype)
             dxh, _ = B.circ_fc_backward_f16(B.circ_precompute_spectra_f16(G.dev(wt), dtype=dtype), None, xt, q, p, k, need_dw=False)
             check_half(dxh.float().cpu().numpy(), O.fc_backward_dx(wt, xr), "dx " + what, dtype)
+
+
+# ---- the staged CONV contraction in chunks of pixels, in every form (the shapes and what they reach: conv_chunk_cases.py)
+@pytest.mark.parametrize("N,p,q,k,H,W,r,stride,pad", [dims for dims, _ in CONV_CHUNK_CASES])
+def test_conv_contraction_chunks(N, p, q, k, H, W, r, stride, pad):
+    rng = np.random.default_rng(N * 1000 + H)
+    w = (rng.standard_normal((r, r, p, q, k)) / np.sqrt(r * r * q * k)).astype(np.float32)
+    x = rng.uniform(-1, 1, (N, q * k, H, W)).astype(np.float32)
+    what = f"chunks N={N} {p}x{q} k={k} {H}x{W} r={r} pad={pad} stride={stride}"
+    check(G.gpu_conv_forward(w, x, None, pad=pad, stride=stride), O.conv_forward(w, x, None, pad=pad, stride=stride), "fwd " + what)
+    if stride == 1:                                                # the transposed grid with reflected offsets
+        dy = rng.uniform(-1, 1, (N, p * k, O.conv_out_size(H, r, pad, 1), O.conv_out_size(W, r, pad, 1))).astype(np.float32)
+        dx, _ = G.gpu_conv_backward(w, x, dy, pad, need_dw=False)
+        check(dx, O.conv_backward_dx(w, dy, H, W, pad), "dx " + what)

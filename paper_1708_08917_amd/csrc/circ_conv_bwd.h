@@ -16,6 +16,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "circ_conv_lds.h"
+
 namespace circ {
 
 // Partial weight-gradient spectra on the matrix cores.  Block (x = pixel chunk, y = frequency f,
@@ -252,7 +254,6 @@ __global__ __launch_bounds__(256) void conv_dw_lds_kernel(const float2* __restri
       }
     }
     __syncthreads();
-    // wave w takes pixels w, w + 4, ...: four at a time (operands first, then 16 matrix instructions)
     auto mac = [&](int e, float2 dv, float2 xv) {
       accR[e] = __builtin_amdgcn_mfma_f32_4x4x1f32(dv.x, xv.x, accR[e], 0, 0, 0);
       accI[e] = __builtin_amdgcn_mfma_f32_4x4x1f32(dv.y, xv.x, accI[e], 0, 0, 0);
@@ -265,6 +266,7 @@ __global__ __launch_bounds__(256) void conv_dw_lds_kernel(const float2* __restri
     };
     int pix = wave;
     if constexpr (PAIR) {
+      // wave w takes pixels w, w + 4, ...: four at a time (operands first)
       for (; pix + 12 < npx; pix += 16) {
         float dv[4], xv[4];
 #pragma unroll
@@ -277,7 +279,25 @@ __global__ __launch_bounds__(256) void conv_dw_lds_kernel(const float2* __restri
       }
       for (; pix < npx; pix += 4) accR[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(dslf[2 * pix], xslf[2 * tap(pix)], accR[0], 0, 0, 0);
     } else {
-      for (; pix + 12 < npx; pix += 16) {
+      // whole groups of 32 pixels: eight consecutive ones per wave; group g (and g + 8) of the instruction fetches dY^ of pixel g,
+      // and the instruction hands it to all groups (CBSZ = 4)
+      const int whole = npx & ~31;
+      for (pix = wave * 8; pix < whole; pix += 32) {
+        const float2 dv = dsl[pix + (blk & 7)];
+        const float ndx = -dv.x;
+        float2 xv[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) xv[u] = xsl[tap(pix + u)];
+        unrolled<8>([&](auto U) {
+          constexpr int u = decltype(U)::value;
+          accR[u & 1] = mfma_bcast<u>(dv.x, xv[u].x, accR[u & 1]);
+          accI[u & 1] = mfma_bcast<u>(dv.y, xv[u].x, accI[u & 1]);
+          accR[u & 1] = mfma_bcast<u>(dv.y, xv[u].y, accR[u & 1]);
+          accI[u & 1] = mfma_bcast<u>(ndx, xv[u].y, accI[u & 1]);
+        });
+      }
+      // the rest: pixels w, w + 4, ... (eight in a row would leave most of the work to one wave)
+      for (pix = whole + wave; pix + 12 < npx; pix += 16) {
         float2 dv[4], xv[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -425,8 +445,13 @@ __global__ __launch_bounds__(1024) void bias_grad_column_kernel(const float* __r
 // here groups 0-7 and 8-15 take the first eight offsets at two pixels, one in the upper and one in the lower half
 // of the band's rows (so that the two differ by a constant address), and the ninth offset runs by itself with
 // a pixel of its own per group: 1/2 + 1/16 instructions and LDS reads per pixel where the form above
-// has 1.  Both are what that kernel spends its time on (LDS as busy as the matrix cores, 256 -> 256 channels
-// 28x28 batch 32: 36 us, 32 us in this form; staging takes most of the rest).  The halves and the groups are added at the end, in a fixed order.
+// has 1.  dY^ of eight pixels is one LDS read, handed out by the instruction (CBSZ); with a read per pixel, instructions
+// and LDS reads that only carry operands (and accumulators that the compiler moved between registers at every step) took
+// more issue slots than the products: 256 -> 256 channels 28x28 batch 32: 28.8 -> 26.0 us, 64 -> 256 channels 56x56 batch 16
+// 57.7 -> 50.9, 13x13 4x4 blocks of 96 14.2 -> 13.3.  Without staging it would be 22.7 us of the 28.8, with neither bank conflicts
+// (rows and planes pitched for it) nor moves 25.5, and requesting the next chunk ahead of the products made it
+// slower, 31.6: issue of address and scalar instructions and the start and end of a workgroup are most of what is left.
+// The halves and the groups are added at the end, in a fixed order.
 // Dynamic LDS: 4 * (S(((2*BRh - 1)*stride + 3) * (W + 2*pad)) + S(2*BRh*Wo)) float2, BRh = ceil(BR / 2); rows of dY^ and
 // X^ past the band are zeros.
 __global__ __launch_bounds__(256) void conv_dw9_kernel(const float2* __restrict__ dyh, const float2* __restrict__ xh,
@@ -507,19 +532,29 @@ __global__ __launch_bounds__(256) void conv_dw9_kernel(const float2* __restrict_
     auto tap = [&](int pix) -> int {              // staged element of output pixel pix of a half, offset (0, 0): stride*(hl*Wp + wo)
       return stride * (pix + int(__umulhi(unsigned(pix), mul_wo)) * (Wp - Wo));
     };
-    // eight offsets, pixels pix and hpx + pix: wave w takes w, w + 4, ..., four at a time
-    int pix = wave;
-    for (; pix + 12 < hpx; pix += 16) {
-      float2 dv[4], xv[4];
+    // eight offsets, pixels pix and hpx + pix, eight of them at a time: wave w takes the runs w, w + 4, ...; group g of a half
+    // fetches dY^ of the run's pixel g, and the instruction hands it to the half's other groups (CBSZ = 3)
+    auto run = [&](int pix, auto WHOLE) {
+      const int left = hpx - pix;                 // (at least 1; WHOLE: at least 8)
+      const float2 dv = dsl[pix + (WHOLE.value ? tap8 : min(tap8, left - 1))];
+      const float ndx = -dv.x;
+      float2 xv[8];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        dv[u] = dsl[pix + 4 * u];
-        xv[u] = xsl[tap(pix + 4 * u)];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) mac(accR[u & 1], accI[u & 1], dv[u], xv[u]);
-    }
-    for (; pix < hpx; pix += 4) mac(accR[0], accI[0], dsl[pix], xsl[tap(pix)]);
+      for (int u = 0; u < 8; ++u)
+        if (WHOLE.value || u < left) xv[u] = xsl[tap(pix + u)];
+      unrolled<8>([&](auto U) {
+        constexpr int u = decltype(U)::value;
+        if (WHOLE.value || u < left) {
+          accR[u & 1] = __builtin_amdgcn_mfma_f32_4x4x1f32(dv.x, xv[u].x, accR[u & 1], 3, u, 0);
+          accI[u & 1] = __builtin_amdgcn_mfma_f32_4x4x1f32(dv.y, xv[u].x, accI[u & 1], 3, u, 0);
+          accR[u & 1] = __builtin_amdgcn_mfma_f32_4x4x1f32(dv.y, xv[u].y, accR[u & 1], 3, u, 0);
+          accI[u & 1] = __builtin_amdgcn_mfma_f32_4x4x1f32(ndx, xv[u].y, accI[u & 1], 3, u, 0);
+        }
+      });
+    };
+    int pix = wave * 8;
+    for (; pix + 8 <= hpx; pix += 32) run(pix, std::true_type{});
+    if (pix < hpx) run(pix, std::false_type{});
     // the ninth offset, pixels 16 s + group
     for (int s = wave * 16; s < npx; s += 64) {
       const int px = min(s + blk, npx - 1);

@@ -683,6 +683,22 @@ def test_conv_dw_3x3(N, p, q, k, H, W, pad, stride):
     check(dw, O.conv_backward_dw(x, dy, k, 3, pad, stride), f"dw 3x3 N={N} {p}x{q} k={k} {H}x{W} pad={pad} stride={stride}")
 
 
+# ---- weight gradient of CONV layers, runs of eight pixels: fewer pixels than a run, one run, a pixel more, ends on either side of
+# the four waves' 32; 3x3 (two halves of a band, pixels of a half: 7, 9, 16, 31, 33) and other filters (pixels of a band: 7, 8, 9, 35, 64)
+@pytest.mark.parametrize("N,p,q,k,H,W,r,stride,pad", [
+    (608, 3, 3, 4, 2, 7, 3, 1, 1), (480, 3, 4, 4, 6, 3, 3, 1, 1), (289, 3, 3, 4, 8, 4, 3, 1, 1), (160, 3, 3, 4, 2, 31, 3, 1, 1),
+    (129, 5, 3, 4, 6, 11, 3, 1, 1),
+    (2, 5, 3, 4, 1, 7, 5, 1, 2), (3, 3, 3, 8, 4, 2, 5, 1, 2), (2, 3, 4, 4, 3, 3, 5, 1, 2), (35, 4, 3, 4, 5, 7, 5, 1, 2), (1, 3, 6, 4, 8, 8, 5, 1, 2),
+    (2, 4, 4, 8, 10, 10, 2, 2, 0), (3, 3, 3, 4, 5, 4, 1, 1, 0),
+])
+def test_conv_dw_runs_of_pixels(N, p, q, k, H, W, r, stride, pad):
+    w = (RNG.standard_normal((r, r, p, q, k)) / np.sqrt(r * r * q * k)).astype(np.float32)
+    x = RNG.uniform(-1, 1, (N, q * k, H, W)).astype(np.float32)
+    dy = RNG.uniform(-1, 1, (N, p * k, O.conv_out_size(H, r, pad, stride), O.conv_out_size(W, r, pad, stride))).astype(np.float32)
+    _, dw = G.gpu_conv_backward(w, x, dy, pad, need_dx=False, stride=stride)
+    check(dw, O.conv_backward_dw(x, dy, k, r, pad, stride), f"dw runs N={N} {p}x{q} k={k} {H}x{W} r={r} pad={pad} stride={stride}")
+
+
 # ---- backward-data of strided layers, one residue class of pixels at a time: classes without a tap (stride above
 # the filter size), stride above the image size, classes of different sizes, several chunks per class, padding
 @pytest.mark.parametrize("N,p,q,k,H,W,r,pad,stride", [

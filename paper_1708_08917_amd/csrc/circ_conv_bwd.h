@@ -447,7 +447,7 @@ __global__ __launch_bounds__(1024) void bias_grad_column_kernel(const float* __r
 // a pixel of its own per group: 1/2 + 1/16 instructions and LDS reads per pixel where the form above
 // has 1.  dY^ of eight pixels is one LDS read, handed out by the instruction (CBSZ); with a read per pixel, instructions
 // and LDS reads that only carry operands (and accumulators that the compiler moved between registers at every step) took
-// more issue slots than the products: 256 -> 256 channels 28x28 batch 32: 28.8 -> 26.0 us, 64 -> 256 channels 56x56 batch 16
+// more issue slots than the products: 256 -> 256 channels 28x28 batch 32: 28.8 -> 26.0 us, 256 -> 128 channels 56x56 batch 16
 // 57.7 -> 50.9, 13x13 4x4 blocks of 96 14.2 -> 13.3.  Without staging it would be 22.7 us of the 28.8, with neither bank conflicts
 // (rows and planes pitched for it) nor moves 25.5, and requesting the next chunk ahead of the products made it
 // slower, 31.6: issue of address and scalar instructions and the start and end of a workgroup are most of what is left.
